@@ -23,7 +23,7 @@
  * synchronises, keeps no pointer after the call returns and holds no state
  * between calls. C must not overlap A or B. Any alignment is accepted;
  * operands whose shapes and alignment suit a tuned tile take the fast
- * kernels, everything else a bounds-checked kernel.
+ * kernels, everything else bounds-checked ones.
  * Scratch memory: the plain entry points (gemm_f16_f32, gemm_s8_s32,
  * gemm_s4_s32, gemm_scaled) use none; they only choose kernels that need no
  * scratch. Split K, the INT4 kernels fed by an FP6 conversion pre-pass and

@@ -5,9 +5,9 @@
 // operand run straight from global memory with per-element bounds checks
 // (out-of-range elements read as zero, which adds nothing to the sums), then
 // issues one MFMA (FP16, INT8) or one MFMA on exactly sign-extended INT4
-// values. Stores are bounds-checked too. This kernel carries the ragged edges
-// and unaligned operands the tiled kernels do not accept; it also serves K = 0
-// (no K-steps: C is written with zeros).
+// values. Stores are bounds-checked too. This kernel carries what neither the
+// tiled kernels nor ragged_gemm.hpp accept: rows shorter than 16 bytes, INT4
+// with K >= 131072, K = 0 (no K-steps: C is written with zeros).
 #pragma once
 
 #include "device_common.hpp"

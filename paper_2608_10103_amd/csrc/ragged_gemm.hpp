@@ -1,0 +1,110 @@
+// ragged_gemm.hpp - LDS-tiled kernel for rows of any length and alignment.
+//
+// The pipelined kernels copy rows in 16-byte pieces straight to LDS, so they
+// need 16-byte aligned rows and K in whole slices. This one takes every other
+// problem whose rows hold at least 16 bytes: it loads 16 bytes per lane from
+// any byte address into registers (global loads need no alignment) and
+// writes them to LDS where the direct copy would have put them, so operand
+// reads, MFMAs and epilogue are the tiled kernels'.
+//
+//  * The whole slices of K run through the register-staged schedule
+//    (rs_slice): two LDS buffers, NSETS slices of loads in flight.
+//  * The rest of K is one more slice, loaded first and kept in registers. A
+//    16-byte chunk that begins at row byte o is loaded from o when the row
+//    holds it whole, else from the row's last 16 bytes; the bytes before o
+//    are then shifted out and zeros take the place of those past the end. No
+//    load leaves its row, so none leaves the operand, and FP16 sums never
+//    meet a neighbouring row's infinity or NaN.
+//
+// What bounds it: the LDS, written through registers and read by few MFMAs
+// per operand (64 x 64: 48 KiB of LDS traffic per slice against 128 MFMA
+// cycles). Against the per-element kernel that served these problems
+// before: FP16 1000^3 78 -> 8.6 us, INT8 269 x 2124 x 169 15 -> 4.5 us; the
+// direct-copy kernels take 8.2 us at 1000 x 1000 x 1024, 75.0 (here 92.2 at
+// 3000^3) at 3000 x 3000 x 3008.
+#pragma once
+
+#include "tiled_gemm.hpp"
+
+namespace mpg {
+
+// Chunk at row byte o, loaded from the row's last 16 bytes where o > Kb - 16:
+// its bytes in place, zeros past the end.
+__device__ __forceinline__ i32x4 rg_tail(i32x4 x, int o, int Kb) {
+    const int s = o - (Kb - 16);  // bytes to shift out; 16 and more: nothing left
+    if (s <= 0) return x;
+    unsigned __int128 v = __builtin_bit_cast(unsigned __int128, x);
+    v = s >= 16 ? 0 : v >> (8 * s);
+    return __builtin_bit_cast(i32x4, v);
+}
+
+// C = A * B, rows of Kb >= 16 bytes at any address; INT4 with K < 131072
+// (sums carried times 256).
+template <int DT, class T, int NSETS>
+__global__ __launch_bounds__(T::NTHREADS, 2) void ragged_gemm(const uint8_t *__restrict__ A,
+                                                             const uint8_t *__restrict__ B,
+                                                             void *__restrict__ Cv, int M, int N, int Kb,
+                                                             int tiles_m, int tiles_n, EpiParams epi) {
+    static_assert(T::STAGES == 2 && T::KCH % 2 == 0, "two LDS buffers, an even number of K-chunks");
+    typedef typename Acc<DT, T::MS>::type acc_t;
+    constexpr int DPW = T::DMA_PER_WAVE;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[T::LDS_BYTES];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane % T::MS, h = lane / T::MS;
+    const int wm = wave / T::WGN, wn = wave % T::WGN;
+    int tm, tn;
+    tile_coords(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, T::GROUP_M, tm, tn);
+
+    acc_t acc[T::FM][T::FN];
+#pragma unroll
+    for (int i = 0; i < T::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < T::FN; ++j) acc[i][j] = acc_t{};
+
+    const int KT = Kb / T::BKB;  // whole slices
+    const uint8_t *src[DPW];
+    i32x4 tail[DPW];
+    int off[DPW];
+#pragma unroll
+    for (int j = 0; j < DPW; ++j) {
+        const int d = wave * DPW + j, q = d * T::ROWS_PER_DMA + lane / T::CH;
+        src[j] = stage_src<T>(A, B, M, N, Kb, tm, tn, d, lane);
+        off[j] = KT * T::BKB + ((lane % T::CH) ^ swz<T::CH>(q)) * 16;
+        tail[j] = *reinterpret_cast<const i32x4_any *>(src[j] + (KT * T::BKB - max(off[j] - (Kb - 16), 0)));
+    }
+
+    if (KT > 0) {
+        i32x4 stg[NSETS][DPW], ra[2][T::FM], rb[2][T::FN];
+        gload_part<T, 0, DPW>(stg[0], src, 0);
+        swrite_part<T, 0, DPW>(lds, stg[0], wave, lane, 0);
+        gload_part<T, 0, DPW>(stg[1 % NSETS], src, min(1, KT - 1));
+        if constexpr (NSETS == 2) gload_part<T, 0, DPW>(stg[0], src, min(2, KT - 1));
+        wait_vm_barrier<63>();
+        load_runs<T>(lds, 0, wm, wn, r, h, ra[0], rb[0]);
+        int kt = 0;
+        if constexpr (NSETS == 1) {
+            for (; kt < KT; ++kt)
+                rs_slice<DT, T, 0, 1>(lds, src, wave, lane, kt, KT, wm, wn, r, h, stg, ra, rb, acc);
+        } else {
+            for (; kt + 1 < KT; kt += 2) {
+                rs_slice<DT, T, 1, 2>(lds, src, wave, lane, kt, KT, wm, wn, r, h, stg, ra, rb, acc);
+                rs_slice<DT, T, 0, 2>(lds, src, wave, lane, kt + 1, KT, wm, wn, r, h, stg, ra, rb, acc);
+            }
+            if (kt < KT) rs_slice<DT, T, 1, 2>(lds, src, wave, lane, kt, KT, wm, wn, r, h, stg, ra, rb, acc);
+        }
+    }
+    if (KT * T::BKB < Kb) {
+        __syncthreads();
+        uint8_t *p = lds + wave * DPW * 1024 + lane * 16;
+#pragma unroll
+        for (int j = 0; j < DPW; ++j) *reinterpret_cast<i32x4 *>(p + j * 1024) = rg_tail(tail[j], off[j], Kb);
+        __syncthreads();
+        compute_stage<DT, T>(lds, wm, wn, r, h, acc);
+    }
+    pf_store<DT, T>(epi, Cv, acc, tm, tn, M, N);
+}
+
+}  // namespace mpg

@@ -528,12 +528,15 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_pf(const uint8_t *_
 // loads re-read the last slice, the surplus writes land in a buffer no one
 // reads again), so every slice body is one scheduling region.
 
+// 16 bytes at any address: global loads need no alignment.
+typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
 template <class T, int J0, int J1>
 __device__ __forceinline__ void gload_part(i32x4 (&reg)[T::DMA_PER_WAVE], const uint8_t *const *src,
                                            int kt) {
 #pragma unroll
     for (int j = J0; j < J1; ++j)
-        reg[j] = *reinterpret_cast<const i32x4 *>(src[j] + (size_t)kt * T::BKB);
+        reg[j] = *reinterpret_cast<const i32x4_any *>(src[j] + (size_t)kt * T::BKB);
 }
 
 template <class T, int J0, int J1>

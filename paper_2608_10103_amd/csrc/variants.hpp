@@ -310,6 +310,14 @@ constexpr int kNumF16 = kNumCommon, kNumS8 = kNumCommon, kNumS4 = kNumCommon + k
 // Kernel of the transposed-B entry point (tposeb.hip): F16 or S8, else null.
 const void *tposeb_kernel(int dtype);
 
+// Kernels for rows of any length and alignment (ragged.hip), by tile side
+// (64 or 128).
+struct RaggedKernel {
+    const void *fn;
+    int bm, bn, threads;
+};
+RaggedKernel ragged_kernel(int dtype, int tile);
+
 extern const Variant kF16[];
 extern const Variant kS8[];
 extern const Variant kS4[];

@@ -264,6 +264,43 @@ def test_ragged_large(dtype):
                       f"{dtype} {M}x{N}x{K} {mp.variant_name(dtype, v)}")
 
 
+# Row bytes (INT4: half as many k again) around one 16-byte load, one and two
+# K-slices of 128 bytes; 64 x 64 tiles, and 128 x 128 ones (at least 128 of
+# them) with one ragged tile on each side.
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("M,N", [(70, 131), (1500, 1409)])
+def test_any_row_length_and_alignment(dtype, M, N):
+    esz = 2 if dtype == "f16" else 1
+    per = {"f16": 0.5, "s8": 1, "s4": 2}[dtype]  # k per byte
+    for kb in (14, 16, 18, 112, 126, 128, 130, 142, 144, 254, 256, 258, 386, 511 if esz == 1 else 510):
+        for off in (0, esz, 16 - esz):
+            if M > 1000 and (off or kb not in (18, 128, 142, 386)):
+                continue
+            A, B = si.gen_operands(dtype, M, N, int(kb * per), seed=kb * 31 + off)
+            bufs = []
+            for X in (A, B):  # surrounded by bytes that are no number (FP16: NaN)
+                raw = torch.full((X.nbytes + 64,), 0xFF, dtype=torch.uint8, device="cuda")
+                raw[16 + off:16 + off + X.nbytes] = torch.from_numpy(X.view(np.uint8).ravel()).cuda()
+                bufs.append(raw)
+            C = torch.empty((M, N), dtype=torch.float32 if dtype == "f16" else torch.int32, device="cuda")
+            assert mp.raw_call(dtype, M, N, int(kb * per), *(x.data_ptr() + 16 + off for x in bufs), C.data_ptr(),
+                               torch.cuda.current_stream().cuda_stream, variant=0) == 0
+            assert_parity(dtype, C.cpu().numpy(), *oracle_gemm(dtype, A, B), f"{dtype} {M}x{N}, {kb} bytes at {off}")
+
+
+def test_ragged_rows_keep_infinities_apart():
+    """A row of infinities reaches its own row of C only: the slice that ends
+    a row takes nothing from the next one."""
+    for K in (63, 65, 1001):
+        A, B = si.gen_operands("f16", 67, 66, K, seed=K)
+        A[5], B[7] = np.inf, -np.inf
+        C = gpu_gemm("f16", A, B)
+        bad = ~np.isfinite(C)
+        want = np.zeros_like(bad)
+        want[5], want[:, 7] = True, True
+        assert np.array_equal(bad, want), K
+
+
 @pytest.mark.parametrize("dtype", DTYPES)
 def test_k_zero_writes_zeros(dtype):
     M, N = 70, 40
