@@ -953,6 +953,22 @@ hipError_t run(int dtype, int variant, int splits, int M, int N, int K, const vo
     return launch(dtype, table(dtype)[ch.variant], ch.splits, ch.sk, M, N, K, A, B, C, epi, ch.plan, ws, stream);
 }
 
+// Tile of the transposed-B kernel: the smallest of 64 x 64 and 64 x 128 whose
+// tiles fit one round of the 256 CUs (more of them busy, little per CU), else
+// 128 x 128, or 256 x 256 from 144 such tiles up (as for column-major B).
+// Graph replays on MI355X, us with 64 x 64 / 64 x 128 / 128 x 128 / 256 x 256
+// tiles: INT8 105 x 2560 x 4096 (80 tiles of 64 x 64) 9.9 / 12.0 / 16.5 /
+// 49.7, 512 x 4096 x 4096 (512, 256 of 64 x 128) 20.9 / 17.2 / 18.8 / 50.6,
+// 1024 x 4096 x 4096 (512 of 64 x 128) 36.9 / 32.2 / 25.4 / 56.5; FP16
+// 3292 x 3840 x 2560 (195 of 256 x 256) 127.9 / 125.1 / 104.1 / 74.8, 2048^3
+// (64) 32.9 / 31.8 / 25.6 / 56.4.
+int tposeb_tile(int M, int N) {
+    const auto tiles = [&](long bm, long bn) { return (M + bm - 1) / bm * (N / bn); };
+    if (tiles(64, 64) <= 256) return TB_64;
+    if (tiles(64, 128) <= 256) return TB_64X128;
+    return tiles(256, 256) >= 144 ? TB_256 : TB_128;
+}
+
 // ---- scratch for callers that cannot allocate (mpgemm_gemm_noalloc) ----
 // A file-scope device array: each GPU the library runs on holds its own copy
 // until the process ends. Host code must not use the name as an address (it
@@ -998,17 +1014,16 @@ hipError_t mpgemm_gemm_bt(int dtype, int M, int N, int K, const void *A, const v
     if (!valid_args(dtype, M, N, K, A, B, C)) return hipErrorInvalidValue;
     if (M == 0 || N == 0) return hipSuccess;
     if (K == 0) return run(dtype, -1, -1, M, N, K, A, B, C, stream, nullptr, Ws{nullptr, 0});  // zero fill
-    typedef TileCfg<256, 256, 2, 4, 128, 2, 4> T;
     const long kb = row_bytes(dtype, K);
-    if (N % T::BN || kb % T::BKB || !aligned(A, 16) || !aligned(B, 16)) return hipErrorInvalidValue;
+    if (N % 256 || kb % 128 || !aligned(A, 16) || !aligned(B, 16)) return hipErrorInvalidValue;
     if (kb > INT_MAX || (long)K * N > (long)INT_MAX * 16) return hipErrorInvalidValue;
     if (dtype == S4 && K >= 131072) return hipErrorInvalidValue;  // INT4 sums carried times 256
     const uint8_t *a = static_cast<const uint8_t *>(A), *b = static_cast<const uint8_t *>(B);
-    int kbi = (int)kb, tiles_m = (M + T::BM - 1) / T::BM, tiles_n = N / T::BN;
+    const TbKernel tk = tposeb_kernel(dtype, tposeb_tile(M, N));
+    int kbi = (int)kb, tiles_m = (M + tk.bm - 1) / tk.bm, tiles_n = N / tk.bn;
     EpiParams epi = plain_epilogue(K);
     void *args[] = {&a, &b, &C, &M, &N, &kbi, &tiles_m, &tiles_n, &epi};
-    return hipLaunchKernel(tposeb_kernel(dtype), dim3(tiles_m * tiles_n), dim3(T::NTHREADS), args, 0,
-                           stream);
+    return hipLaunchKernel(tk.fn, dim3(tiles_m * tiles_n), dim3(tk.threads), args, 0, stream);
 }
 
 hipError_t gemm_f16_f32(int M, int N, int K, const void *A, const void *B, float *C,

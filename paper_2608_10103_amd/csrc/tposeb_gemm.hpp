@@ -18,12 +18,18 @@
 // a column-major INT4 run, so the decode and MFMAs are the column-major
 // kernel's.
 //
-// Everything else is the 8-wave pipelined kernel of tiled_gemm.hpp: 256 x 256
-// tile, 2 x 4 waves of 128 x 64, 128-byte K-slices of A (BKB / es k-rows of
-// B) in a 2-stage ring, operand runs double-buffered in registers, the
-// barrier inside the last K-chunk. FP16, INT8 and INT4. N must fill whole
-// tiles (the copy takes whole B rows of the tile), K whole slices; M may be
-// ragged.
+// Everything else is the pipelined kernel of tiled_gemm.hpp: 128-byte
+// K-slices of A (BKB / es k-rows of B), operand runs double-buffered in
+// registers. Four tiles: 256 x 256 (8 waves of 128 x 64, two stages, runs read
+// a K-chunk ahead, the barrier inside the last chunk) and, where those leave
+// CUs idle, 128 x 128 (8 waves of 64 x 32), 64 x 128 and 64 x 64 (waves of 32
+// x 32), four stages, runs read a whole slice ahead. What bounds the small
+// ones is a workgroup's time per slice: 0.5-0.65 us with 128 x 128 tiles, 0.4
+// with 64 x 64 (FP16; 0.85 and 0.58 read a chunk ahead), so 256 of them at
+// once matter more than bytes: INT8 1024 x 4096 x 4096 56.5 -> 25.4 us, FP16
+// 105 x 2560 x 4096 97.3 -> 26.0 against 256 x 256 tiles alone. FP16, INT8
+// and INT4. N must fill whole tiles (the copy takes whole B rows), K whole
+// slices; M may be ragged.
 #pragma once
 
 #include "tiled_gemm.hpp"
@@ -32,7 +38,7 @@ namespace mpg {
 
 template <int DT, class T>
 struct TB {
-    static_assert(T::MS == 32 && T::BKB == 128 && T::STAGES == 2, "the 128-byte 2-stage pipelined tile");
+    static_assert(T::MS == 32 && T::BKB == 128, "32x32 MFMAs, 128-byte slices");
     static constexpr int EPB2 = DT == F16 ? 1 : (DT == S8 ? 2 : 4);  // elements per 2 bytes
     static constexpr int BK = T::BKB * EPB2 / 2;         // k per slice = B rows per stage
     static constexpr int RB = T::BN * 2 / EPB2;          // bytes of one B row in the tile
@@ -43,29 +49,26 @@ struct TB {
     static constexpr int LPR = 16 / RR;                  // lanes per row in a 16-lane group
     // byte offset of column j within a B row
     static __host__ __device__ constexpr long col_bytes(long j) { return j * 2 / EPB2; }
-    static_assert(A_UNITS % T::DMA_PER_WAVE == 0, "a wave copies only A or only B");
     static_assert(BK * RB == T::BN * T::BKB, "B part of a stage is as large as the column-major one");
 };
 
-// Slot of 16-byte chunk c of B row r (row r of the stage's B part). The 16
-// lanes of a transpose read take RR consecutive rows of one 16-column slice
-// (32 bytes per row for FP16, 16 for INT8); rows of 512 (FP16) or 256 (INT8)
-// bytes all start on the same bank, so the chunks are spread by row: the two
-// 16-lane groups that read one 32-column block hit 16 distinct 16-byte bank
-// groups.
-// INT4: rows of 128 bytes, a read's 16 lanes take 16 consecutive rows of one
-// 8-byte column group; rows r and r + 1 start on opposite halves of the
-// 256-byte bank row, so slot (r / 2) % 8 spreads the 16 rows over 16 distinct
-// 8-byte bank pairs.
-template <int DT>
+// Slot of 16-byte chunk c of B row r (row r of the stage's B part, RB bytes):
+// c ^ tb_swz(r). Two neighbouring 16-lane groups of a transpose read take RR
+// consecutive rows (4, 8, 16) of one 32-column slice: 64 (FP16), 32 (INT8) or
+// 16 (INT4) bytes of each, 256 bytes in all. Rows start on the same bank
+// every 256 / RB of them (every row from 256 bytes on), so the rows that
+// share a start are spread over the chunks: the read touches all 64 banks once.
+template <int DT, int RB>
 __host__ __device__ constexpr int tb_swz(int r) {
-    return DT == F16 ? 4 * (r & 3) : (DT == S8 ? 2 * (r & 7) : (r >> 1) & 7);
+    constexpr int SH = RB >= 256 ? 0 : (RB == 128 ? 1 : (RB == 64 ? 2 : 3)), CH = RB / 16 < 16 ? RB / 16 : 16;
+    const int x = r >> SH;
+    return (DT == F16 ? 4 * (x & 3) : (DT == S8 ? 2 * (x & 7) : (x & 15))) & (CH - 1);
 }
 
 // Copy unit d of a stage for lane `lane`: A units as in the pipelined kernel;
 // B unit u (d = A_UNITS + u) takes B rows kt * BK + u * ROWS_PER_UNIT + ...,
 // chunk slot lane % CHB holding logical chunk slot ^ tb_swz(row). Returns the
-// source at slice 0; the per-slice advance is tb_stride().
+// source at slice 0 (tb_issue adds the per-slice advance).
 template <int DT, class T>
 __device__ __forceinline__ const uint8_t *tb_src(const uint8_t *A, const uint8_t *B, int M, int N,
                                                  int Kb, int tm, int tn, int d, int lane) {
@@ -73,7 +76,7 @@ __device__ __forceinline__ const uint8_t *tb_src(const uint8_t *A, const uint8_t
     if (d < P::A_UNITS) return stage_src<T>(A, B, M, N, Kb, tm, tn, d, lane);
     const int u = d - P::A_UNITS;
     const int r = u * P::ROWS_PER_UNIT + lane / P::CHB;  // B row within the stage
-    const int c = (lane % P::CHB) ^ tb_swz<DT>(r);
+    const int c = (lane % P::CHB) ^ tb_swz<DT, P::RB>(r);
     return B + (size_t)r * P::col_bytes(N) + (size_t)tn * P::RB + c * 16;
 }
 
@@ -100,7 +103,7 @@ __device__ __forceinline__ void tb_load_runs(const uint8_t *st, int kc, int wm, 
         for (int t = 0; t < 2; ++t) {
             // k rows of this read: chunk kc's 16 (FP16) / 32 (INT8) / 64 (INT4) k, half g / 2, part t
             const int row = kc * (2 * 2 * P::RR) + (g >> 1) * (2 * P::RR) + t * P::RR + j16 / P::LPR;
-            const uint8_t *p = sb + row * P::RB + ((((byte >> 4) ^ tb_swz<DT>(row))) << 4) + (byte & 15);
+            const uint8_t *p = sb + row * P::RB + ((((byte >> 4) ^ tb_swz<DT, P::RB>(row))) << 4) + (byte & 15);
             typedef __attribute__((address_space(3))) void lds_void_t;
             if constexpr (DT == F16) {
                 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -127,15 +130,15 @@ __device__ __forceinline__ void tb_load_runs(const uint8_t *st, int kc, int wm, 
     }
 }
 
-// This wave's copies of slice kt into buffer `stage`: A waves advance by the
-// slice's bytes, B waves by its BK rows.
+// This wave's copies of slice kt into buffer `stage`: A units advance by the
+// slice's bytes, B units by its BK rows (`stride` bytes).
 template <int DT, class T>
 __device__ __forceinline__ void tb_issue(uint8_t *lds, const uint8_t *const *src, int wave, int stage,
                                          int kt, long stride) {
 #pragma unroll
     for (int j = 0; j < T::DMA_PER_WAVE; ++j) {
         const int d = wave * T::DMA_PER_WAVE + j;
-        dma16(src[j] + (size_t)kt * stride, lds + stage * T::STAGE_BYTES + d * 1024);
+        dma16(src[j] + kt * (d < TB<DT, T>::A_UNITS ? (long)T::BKB : stride), lds + stage * T::STAGE_BYTES + d * 1024);
     }
 }
 
@@ -169,6 +172,77 @@ __device__ __forceinline__ void tb_slice(uint8_t *lds, const uint8_t *const *src
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// Slice-ahead schedule, for wave tiles of few MFMAs: a transpose read takes
+// so long that the schedule above, one K-chunk ahead, waits for it at every
+// chunk. All operand runs of slice kt + 1 are read at once while slice kt's
+// MFMAs run from registers; one wait + barrier per slice frees buffer kt % S
+// (every wave holds slice kt in registers) and publishes slice kt + 1.
+template <class T>
+constexpr bool kTbAhead = 8 * (T::FM + T::FN) * T::KCH + T::FM * T::FN * T::NV <= 128;
+
+// Wait with the copies of at most `slices` slices left in flight, barrier.
+template <class T, int MAX>
+__device__ __forceinline__ void tb_wait_slices(int slices) {
+    if constexpr (MAX > 0) {
+        if (slices >= MAX) return wait_vm_barrier<MAX * T::DMA_PER_WAVE>();
+        tb_wait_slices<T, MAX - 1>(slices);
+    } else {
+        wait_vm_barrier<0>();
+    }
+}
+
+template <int DT, class T, bool ISSUE>
+__device__ __forceinline__ void tb_slice_ahead(uint8_t *lds, const uint8_t *const *src, long stride, int wave, int kt,
+                                               int KT, int wm, int wn, int lane, const i32x4 (&ca)[T::KCH][T::FM],
+                                               const i32x4 (&cb)[T::KCH][T::FN], i32x4 (&na)[T::KCH][T::FM],
+                                               i32x4 (&nb)[T::KCH][T::FN],
+                                               typename Acc<DT, 32>::type (&acc)[T::FM][T::FN]) {
+    constexpr int S = T::STAGES;
+    // a wait for the reads that the compiler knows of: with only the one in
+    // the asm it would wait again, after the next reads
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    // in flight after the wait: slices kt + 2 .. kt + S - 1, or what is left
+    if constexpr (ISSUE) wait_vm_barrier<(S - 2) * T::DMA_PER_WAVE>();
+    else tb_wait_slices<T, S - 2>(KT - 2 - kt);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint8_t *st = lds + ((kt + 1) % S) * T::STAGE_BYTES;
+    // (after the last slice this reads a buffer nobody uses again; harmless)
+#pragma unroll
+    for (int kc = 0; kc < T::KCH; ++kc) tb_load_runs<DT, T>(st, kc, wm, wn, lane, na[kc], nb[kc]);
+    if constexpr (ISSUE) tb_issue<DT, T>(lds, src, wave, kt % S, kt + S, stride);
+#pragma unroll
+    for (int kc = 0; kc < T::KCH; ++kc) mma_runs<DT, T, 0, T::FM * T::FN>(ca[kc], cb[kc], acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int DT, class T>
+__device__ __forceinline__ void tb_accumulate_ahead(uint8_t *lds, const uint8_t *const *src, long stride, int wave,
+                                                    int KT, int wm, int wn, int lane,
+                                                    typename Acc<DT, 32>::type (&acc)[T::FM][T::FN]) {
+    constexpr int S = T::STAGES;
+    static_assert((S - 1) * T::DMA_PER_WAVE <= 63, "vmcnt range");
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        if (s < KT) tb_issue<DT, T>(lds, src, wave, s, s, stride);
+    tb_wait_slices<T, S - 1>(KT - 1);
+    i32x4 a0[T::KCH][T::FM], b0[T::KCH][T::FN], a1[T::KCH][T::FM], b1[T::KCH][T::FN];
+#pragma unroll
+    for (int kc = 0; kc < T::KCH; ++kc) tb_load_runs<DT, T>(lds, kc, wm, wn, lane, a0[kc], b0[kc]);
+    int kt = 0;
+    for (; kt + 1 + S < KT; kt += 2) {
+        tb_slice_ahead<DT, T, true>(lds, src, stride, wave, kt, KT, wm, wn, lane, a0, b0, a1, b1, acc);
+        tb_slice_ahead<DT, T, true>(lds, src, stride, wave, kt + 1, KT, wm, wn, lane, a1, b1, a0, b0, acc);
+    }
+    // at most one more slice issues a copy; then the rest
+    if (kt + S < KT) tb_slice_ahead<DT, T, true>(lds, src, stride, wave, kt, KT, wm, wn, lane, a0, b0, a1, b1, acc);
+    else tb_slice_ahead<DT, T, false>(lds, src, stride, wave, kt, KT, wm, wn, lane, a0, b0, a1, b1, acc);
+    for (++kt; kt < KT; kt += 2) {
+        tb_slice_ahead<DT, T, false>(lds, src, stride, wave, kt, KT, wm, wn, lane, a1, b1, a0, b0, acc);
+        if (kt + 1 >= KT) break;
+        tb_slice_ahead<DT, T, false>(lds, src, stride, wave, kt + 1, KT, wm, wn, lane, a0, b0, a1, b1, acc);
+    }
+}
+
 // C = A * B with B(k, j) at element k * N + j. N a multiple of BN; K bytes
 // per A row (Kb) a multiple of BKB.
 template <int DT, class T>
@@ -193,8 +267,8 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_tb(const uint8_t *_
 #pragma unroll
     for (int j = 0; j < T::DMA_PER_WAVE; ++j)
         src[j] = tb_src<DT, T>(A, B, M, N, Kb, tm, tn, wave * T::DMA_PER_WAVE + j, lane);
-    // per-slice advance: A waves by the slice's bytes, B waves by BK rows of B
-    const long stride = (wave * T::DMA_PER_WAVE < P::A_UNITS) ? (long)T::BKB : (long)P::BK * P::col_bytes(N);
+    // per-slice advance of B's units: BK rows
+    const long stride = (long)P::BK * P::col_bytes(N);
 
     acc_t acc[T::FM][T::FN];
 #pragma unroll
@@ -203,17 +277,21 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_tb(const uint8_t *_
         for (int j = 0; j < T::FN; ++j) acc[i][j] = acc_t{};
 
     const int KT = Kb / T::BKB;
+    if constexpr (kTbAhead<T>) {
+        tb_accumulate_ahead<DT, T>(lds, src, stride, wave, KT, wm, wn, lane, acc);
+    } else {
 #pragma unroll
-    for (int s = 0; s < S; ++s)
-        if (s < KT) tb_issue<DT, T>(lds, src, wave, s, s, stride);
-    if (KT >= S) wait_vm_barrier<(S - 1) * T::DMA_PER_WAVE>();
-    else wait_vm_barrier<0>();
+        for (int s = 0; s < S; ++s)
+            if (s < KT) tb_issue<DT, T>(lds, src, wave, s, s, stride);
+        if (KT >= S) wait_vm_barrier<(S - 1) * T::DMA_PER_WAVE>();
+        else wait_vm_barrier<0>();
 
-    i32x4 ra[2][T::FM], rb[2][T::FN];
-    tb_load_runs<DT, T>(lds, 0, wm, wn, lane, ra[0], rb[0]);
-    int kt = 0;
-    for (; kt + S < KT; ++kt) tb_slice<DT, T, true>(lds, src, stride, wave, kt, wm, wn, lane, ra, rb, acc);
-    for (; kt < KT; ++kt) tb_slice<DT, T, false>(lds, src, stride, wave, kt, wm, wn, lane, ra, rb, acc);
+        i32x4 ra[2][T::FM], rb[2][T::FN];
+        tb_load_runs<DT, T>(lds, 0, wm, wn, lane, ra[0], rb[0]);
+        int kt = 0;
+        for (; kt + S < KT; ++kt) tb_slice<DT, T, true>(lds, src, stride, wave, kt, wm, wn, lane, ra, rb, acc);
+        for (; kt < KT; ++kt) tb_slice<DT, T, false>(lds, src, stride, wave, kt, wm, wn, lane, ra, rb, acc);
+    }
 
     const long row0 = (long)tm * T::BM + wm * T::WTM;
     const long col0 = (long)tn * T::BN + wn * T::WTN + (lane % 32);

@@ -307,10 +307,15 @@ constexpr int kNumCommon = 69;
 constexpr int kNumFp6 = 17;
 constexpr int kNumF16 = kNumCommon, kNumS8 = kNumCommon, kNumS4 = kNumCommon + kNumFp6;
 
-// Kernel of the transposed-B entry point (tposeb.hip): F16 or S8, else null.
-const void *tposeb_kernel(int dtype);
+// Kernels of the transposed-B entry point (tposeb.hip), by tile.
+enum TbTile { TB_64 = 0, TB_64X128 = 1, TB_128 = 2, TB_256 = 3 };
+struct TbKernel {
+    const void *fn;
+    int bm, bn, threads;
+};
+TbKernel tposeb_kernel(int dtype, int tile);
 
-// Kernels for rows of any length and alignment (ragged.hip), by tile side
+// Kernels for rows of any length and alignment (tposeb.hip), by tile side
 // (64 or 128).
 struct RaggedKernel {
     const void *fn;

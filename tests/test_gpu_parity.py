@@ -982,6 +982,20 @@ def test_transposed_b_parity(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "s8", "s4"])
+@pytest.mark.parametrize("M,N", [(63, 256), (129, 512), (130, 8192), (520, 4096), (2100, 256)])
+def test_transposed_b_every_tile(dtype, M, N):
+    """Each tile of the transposed-B kernel (64 x 64, 64 x 128, 128 x 128; the
+    256 x 256 one runs at full size below) on ragged M, with one slice, the
+    four-slice ring exactly full, one more, and its steady state with an even
+    and an odd rest."""
+    for slices in (1, 2, 4, 5, 9, 12):
+        K = slices * KSLICE[dtype]
+        A, B = si.gen_operands(dtype, M, N, K, seed=77 + M + slices)
+        C = _gpu_gemm_bt(dtype, A, _to_kn(dtype, B))
+        assert_parity(dtype, C, *oracle_gemm(dtype, A, B), f"{dtype} transposed B {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "s8", "s4"])
 def test_transposed_b_full_size_sampled_rows(dtype):
     """N = 8192 (the measured size): 40 sampled rows against the oracle."""
     n = 8192
