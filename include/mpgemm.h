@@ -217,12 +217,17 @@ int mpgemm_num_variants(int dtype);
 /* Static, NUL-terminated name of a variant ("" if out of range). */
 const char *mpgemm_variant_name(int dtype, int variant);
 
-/* The variant the dtype's entry point runs for these arguments (pointers are
- * only inspected for alignment), or -1 if the arguments are invalid. */
+/* The variant the dtype's entry point chooses for these arguments (pointers
+ * are only inspected for alignment), or -1 if the arguments are invalid.
+ * Where it names a tile whose workgroups leave CUs idle or the streaming
+ * kernel, the entry points (mpgemm_gemm_ws and mpgemm_gemm_noalloc too) run
+ * the same product on one of the small tiles instead ("spread16x16...",
+ * "spread32x32...", "spread64x64_w2x4...") if that is expected to be faster:
+ * same results, no scratch. mpgemm_run_variant runs exactly what it names. */
 int mpgemm_select_variant(int dtype, int M, int N, int K, const void *A, const void *B,
                           const void *C);
 
-/* The variant mpgemm_gemm_ws runs for these arguments with a workspace that
+/* The variant mpgemm_gemm_ws chooses for these arguments with a workspace that
  * holds that variant's scratch (INT4 then takes the FP6 kernels fed by the
  * conversion pre-pass where they are faster), or -1 for invalid arguments. */
 int mpgemm_select_variant_ws(int dtype, int M, int N, int K, const void *A, const void *B,
@@ -249,7 +254,8 @@ hipError_t mpgemm_run_variant(int dtype, int variant, int M, int N, int K, const
  * while the grid stays within 128 workgroups, up to 4 ranges; where those do
  * not apply, the 128x128 tiles of problems with M or N at most 128 up to 256
  * workgroups, 4 ranges for FP16, 2 for the integer types. The narrow tiles
- * with an eight-slice ring ("..._s8_m16") are never split. */
+ * with an eight-slice ring ("..._s8_m16") and the small tiles are never
+ * split. */
 
 /* Splits the automatic choice uses for this variant and problem when a large
  * enough workspace is given (1 = none), or -1 for an invalid dtype, variant

@@ -287,6 +287,10 @@ constexpr int kNumNarrowW = 3;
 // 32 x 128, their mirrors 64 x 32 and 128 x 32, then 64 x 64.
 constexpr int V_DEEP = 59;          // spread32x64_w1x2_k128_s8_m16
 constexpr int kNumDeep = 5;
+// Small tiles (refine), never split: 16 x 16 and 32 x 32 with an eight-slice
+// ring, 32 x 32 with four slices, 64 x 64 with eight waves and five.
+constexpr int V_SMALL = V_DEEP + kNumDeep;  // spread16x16_w1x1_k128_s8_m16
+constexpr int kNumSmall = 4;
 
 // Problems the narrow tiles serve: at most 1024 rows on the small side and
 // at least 1024 on the large one, with the small side at most 512 rows or
@@ -324,6 +328,11 @@ bool is_deep(int dtype, const Variant &v) {
     return &v >= t + V_DEEP && &v < t + V_DEEP + kNumDeep;
 }
 
+bool is_small(int dtype, const Variant &v) {
+    const Variant *t = table(dtype);
+    return &v >= t + V_SMALL && &v < t + V_SMALL + kNumSmall;
+}
+
 // Splits the entry points use. Only skinny problems (M or N at most 128, the
 // LLM-inference shapes) are split: they stream one large operand from HBM,
 // and splitting K lets more CUs stream it. Measured on MI355X at M = 16,
@@ -337,7 +346,7 @@ bool is_deep(int dtype, const Variant &v) {
 // unsplit, 22.1 us with 2). The narrow tiles with the eight-slice ring are
 // never split: their deeper ring is what the split bought.
 int choose_splits(int dtype, const Variant &v, int M, int N, int K) {
-    if (!v.splitk || v.kind != TILED || is_deep(dtype, v)) return 1;
+    if (!v.splitk || v.kind != TILED || is_deep(dtype, v) || is_small(dtype, v)) return 1;
     if (M > 128 && N > 128 && !is_narrow(dtype, v, M, N)) return 1;
     const bool narrow = is_narrow(dtype, v, M, N);
     // Above 256 rows on the small side the narrow choice runs unsplit: its
@@ -662,6 +671,109 @@ int select_variant(int dtype, int M, int N, int K, const void *A, const void *B,
     return 0;
 }
 
+// ---- small tiles for problems of few tiles (refine) ----
+// With 32 x 64 tiles and larger, a decoding step or a small square runs 32 to
+// 224 workgroups of 40 to 160 KiB of LDS: CUs stay idle, the others hold one
+// workgroup, and the call lasts as long as one workgroup's walk along K. The
+// small tiles run several workgroups on every CU. They copy more bytes, so
+// they pay only while the walk, not the copies, is what takes the time. The
+// choice compares modelled times (us): a launch, and per K-slice of 128 bytes
+// the time of a workgroup alone on its CU, or its share of the CU where n run
+// there: KT max(alone, n shared), over the rounds of `resident` workgroups
+// per CU. The figures are fitted to graph replays on MI355X with operands
+// that change from call to call, 155 shapes per precision (1 .. 512 x 1536
+// .. 14336 x 1536 .. 14336, 256^3 .. 1408^3): the pick is within 3% of the
+// fastest tile on average and 1.28 (FP16), 1.27 (INT8), 1.21 (INT4) times as
+// fast as the tile chosen before without a workspace, 1.15, 1.22 and 1.18
+// with one (K split). INT4's slices hold twice the k: two MFMAs and a decode
+// per run.
+struct SliceCost {
+    int variant, resident;
+    double alone, shared, alone4, shared4;  // FP16 and INT8; INT4
+};
+const SliceCost kSliceCost[] = {
+    {V_SMALL, 5, .110, .052, .200, .090},        // 16 x 16, one wave, eight slices
+    {V_SMALL + 1, 2, .130, .115, .305, .220},    // 32 x 32, four waves, eight slices
+    {V_SMALL + 2, 4, .165, .105, .300, .184},    // 32 x 32, four waves, four slices
+    {V_SMALL + 3, 2, .235, .260, .400, .516},    // 64 x 64, eight waves, five slices
+    {V_NARROW, 3, .235, .250, .420, .540},       // 32 x 64; 32 x 128; mirrors
+    {V_NARROW + 1, 2, .290, .300, .500, .500},
+    {V_NARROW + 3, 3, .235, .250, .420, .540},
+    {V_NARROW + 4, 2, .290, .300, .500, .500},
+    {V_NARROW64, 2, .280, .320, .420, .500},     // 64 x 64, 64 x 128, 128 x 64
+    {V_NARROW64W8, 1, .285, .340, .745, .745},
+    {V_NARROW64W8 + 1, 1, .285, .340, .745, .745},
+    {V_DEEP, 1, .190, .245, .420, .540},         // 32 x 64, 32 x 128, mirrors, 64 x 64, eight slices
+    {V_DEEP + 1, 1, .250, .300, .500, .500},
+    {V_DEEP + 2, 1, .190, .245, .420, .540},
+    {V_DEEP + 3, 1, .250, .300, .500, .500},
+    {V_DEEP + 4, 1, .235, .260, .435, .560},
+    {V_SPREAD128W8, 1, .330, .500, .745, .745},  // 128 x 128; 64-byte slices
+    {V_SPREAD128W8_K64, 2, .330, .500, .385, .500},
+    {V_SPREAD128_K128, 1, .450, .600, .800, .800},
+    {V_PIPE64, 2, .750, .750, .750, .750},
+};
+constexpr double kLaunchUs = 2.2, kSplitUs = 6.0;  // launch and end; the split's fix-up
+
+// Modelled time of a variant in kSliceCost, or -1.
+double tile_us(int dtype, int variant, int splits, int M, int N, int K) {
+    for (const SliceCost &c : kSliceCost) {
+        if (c.variant != variant) continue;
+        const Variant &v = table(dtype)[variant];
+        const double alone = dtype == S4 ? c.alone4 : c.alone, shared = dtype == S4 ? c.shared4 : c.shared;
+        const long wgs = tile_count(v, M, N) * splits, round = 256L * c.resident;
+        const double slices = (double)row_bytes(dtype, K) / v.bkb / splits;
+        const auto per_slice = [&](long n) { return alone > n * shared ? alone : n * shared; };
+        double t = (double)(wgs / round) * per_slice(c.resident);
+        if (wgs % round) t += per_slice((wgs % round + 255) / 256);
+        return kLaunchUs + slices * t + (splits > 1 ? kSplitUs + splits - 1 : 0.0);
+    }
+    return -1;
+}
+
+// Modelled time of a streaming kernel: K-steps of a wave (whole prefetch
+// groups) times the workgroups of a CU; the small operand's rows, read from
+// L2 by every wave, cost up to half as much again.
+double skinny_us(int dtype, int variant, int M, int N, int K) {
+    const Variant &v = table(dtype)[variant];
+    const int small = M < N ? M : N, large = M < N ? N : M, group = variant == V_SKINNY16_D8 ? 8 : 4;
+    const long steps = (row_bytes(dtype, K) / 64 + SKINNY_WAVES - 1) / SKINNY_WAVES;
+    const long wgs = (large + v.bn - 1) / v.bn;
+    const double step = v.bm > 16 ? 1.5 : (v.bn > 16 ? .55 : (dtype == S4 ? .43 : .33)) + .2 * small / 16;
+    return kLaunchUs + (double)((steps + group - 1) / group * group) * (double)((wgs + 255) / 256) * step;
+}
+
+// The variant a call of the automatic choice runs, given the one that
+// select_variant names and its split: a small tile where the model puts it at
+// least 7% ahead, else the same. A weight matrix past the caches (64 MiB)
+// under an eight-slice tile is left there unless one row of small tiles
+// covers the small side: read once per row, it comes from memory each time
+// (FP16 64 x 8192 x 8192 45 against 40 us); and one row against one past 96
+// MiB is the memory's time either way (1 x 8192 x 8192 28.4 against 26.5).
+int refine(int dtype, int variant, int splits, int M, int N, int K, const void *A, const void *B, const void *C) {
+    const Variant *t = table(dtype);
+    const Variant &v = t[variant];
+    const int small = M < N ? M : N, large = M < N ? N : M;
+    const long bytes = (long)large * row_bytes(dtype, K);
+    double have;
+    if (v.kind == SKINNY) {
+        if (small == 1 && bytes > (96L << 20) && large <= 16 * 512) return variant;
+        have = skinny_us(dtype, variant, M, N, K);
+    } else {
+        have = v.kind == TILED ? tile_us(dtype, variant, splits, M, N, K) : -1;
+    }
+    if (have < 0) return variant;
+    int best = variant;
+    double best_us = 0.93 * have;
+    for (int cand = V_SMALL; cand < V_SMALL + kNumSmall; ++cand) {
+        if (!supports(dtype, t[cand], M, N, K, A, B, C)) continue;
+        if (is_deep(dtype, v) && bytes > (64L << 20) && small > t[cand].bm) continue;
+        const double us = tile_us(dtype, cand, 1, M, N, K);
+        if (us < best_us) best = cand, best_us = us;
+    }
+    return best;
+}
+
 // Caller workspace. Layout: [0, 64 KiB) the split-K and stream-K tile
 // counters (zero before the first such call on a workspace; every call
 // leaves the counters it used zero again), then the zero-point row sums
@@ -882,7 +994,8 @@ struct Choice {
 hipError_t choose(int dtype, int variant, int splits, int M, int N, int K, const void *A, const void *B,
                   const void *C, bool zero_points, size_t ws_bytes, Choice &out) {
     const Variant *t = table(dtype);
-    if (variant < 0) {
+    const bool automatic = variant < 0;
+    if (automatic) {
         // the choice with a workspace where it holds that choice's scratch
         // (the FP6 pre-pass operands; split K is decided below), else the
         // choice without one
@@ -901,6 +1014,13 @@ hipError_t choose(int dtype, int variant, int splits, int M, int N, int K, const
         }
     }
     if (variant >= num_variants(dtype)) return hipErrorInvalidValue;
+    if (automatic) {
+        // (128 x 128 tiles split over a workspace keep it: the small side
+        // that they serve has no large one to spread over the CUs)
+        int sp = choose_splits(dtype, t[variant], M, N, K);
+        if (sp > 1 && ws_plan(t[variant], sp, M, N, K, zero_points, SkPlan{}).total > ws_bytes) sp = 1;
+        if (sp == 1 || variant != V_SPREAD128_K128) variant = refine(dtype, variant, sp, M, N, K, A, B, C);
+    }
     const Variant &v = t[variant];
     if (!supports(dtype, v, M, N, K, A, B, C)) return hipErrorInvalidValue;
     if (splits < 0) {

@@ -64,6 +64,11 @@ typedef TileCfg<32, 128, 1, 4, 128, 8, 4, 16> T32x128_w4_m16_s8;
 typedef TileCfg<64, 32, 2, 1, 128, 8, 4, 16> T64x32_w2_m16_s8;
 typedef TileCfg<128, 32, 4, 1, 128, 8, 4, 16> T128x32_w4_m16_s8;
 typedef TileCfg<64, 64, 2, 2, 128, 8, 4, 16> T64x64_w4_m16_s8;
+// small tiles: several workgroups per CU, more CUs for problems of few tiles
+typedef TileCfg<16, 16, 1, 1, 128, 8, 4, 16> T16x16_w1_m16_s8;
+typedef TileCfg<32, 32, 2, 2, 128, 8, 4, 16> T32x32_w4_m16_s8;
+typedef TileCfg<32, 32, 2, 2, 128, 4, 4, 16> T32x32_w4_m16;
+typedef TileCfg<64, 64, 2, 4, 128, 5, 4, 16> T64x64_w8_m16_s5;
 
 //             BM   BN  WGM WGN  J STG GROUP_M    (J runs of 32 k per stage)
 typedef F6Cfg<256, 256, 2, 4, 4, 3, 4> F6_256x256_w8_s3;
@@ -295,6 +300,10 @@ Variant generic(const char *name) {
      pipelined<DT, T64x32_w2_m16_s8, true>("spread64x32_w2x1_k128_s8_m16"),   \
      pipelined<DT, T128x32_w4_m16_s8, true>("spread128x32_w4x1_k128_s8_m16"), \
      pipelined<DT, T64x64_w4_m16_s8, true>("spread64x64_w2x2_k128_s8_m16"),   \
+     pipelined<DT, T16x16_w1_m16_s8, true>("spread16x16_w1x1_k128_s8_m16"),   \
+     pipelined<DT, T32x32_w4_m16_s8, true>("spread32x32_w2x2_k128_s8_m16"),   \
+     pipelined<DT, T32x32_w4_m16, true>("spread32x32_w2x2_k128_s4_m16"),      \
+     pipelined<DT, T64x64_w8_m16_s5, true>("spread64x64_w2x4_k128_s5_m16"),   \
      wide_sk<DT>("wide256x256_w2x2_k128_m16_sk"),                          \
      pipelined_sk<DT, T256x256_w8_s2, false>("pipe256x256_w2x4_k128_s2_sk"), \
      pipelined_sk<DT, T128x128_w4_s4, true>("spread128x128_w2x2_k128_s4_sk"), \
@@ -303,7 +312,7 @@ Variant generic(const char *name) {
 
 // Number of entries of VARIANT_LIST, and the INT4 table's FP6 variants after
 // them (variants_s4.hip); each table checks its size against these.
-constexpr int kNumCommon = 69;
+constexpr int kNumCommon = 73;
 constexpr int kNumFp6 = 17;
 constexpr int kNumF16 = kNumCommon, kNumS8 = kNumCommon, kNumS4 = kNumCommon + kNumFp6;
 

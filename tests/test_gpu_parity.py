@@ -234,6 +234,7 @@ def test_f16_small_integers_bit_exact(n):
 
 
 EDGE = [1, 2, 3, 31, 33, 100]
+KSLICE = {"f16": 64, "s8": 128, "s4": 256}  # k of a 128-byte slice
 
 
 @pytest.mark.parametrize("dtype", DTYPES)
@@ -362,6 +363,20 @@ def test_argument_errors():
     # a tiled variant refuses shapes off its tile grid
     assert mp.raw_call("s8", 100, 256, 256, pa, pa, pc, variant=1) == INVALID
     torch.cuda.synchronize()
+
+
+# Small tiles (16 x 16, 32 x 32, 64 x 64) through the entry points: one row,
+# one more than a tile on either side, mirrored, a single K-slice and ring
+# lengths around eight.
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("M,N,slices", [(1, 2049, 9), (17, 1100, 8), (33, 2000, 16), (1100, 47, 7), (257, 300, 1),
+                                        (300, 257, 12), (512, 512, 8), (700, 500, 17)])
+def test_small_tiles_through_the_entry_points(dtype, M, N, slices):
+    K = slices * KSLICE[dtype]
+    A, B = si.gen_operands(dtype, M, N, K, seed=M + N + slices)
+    ref, D = oracle_gemm(dtype, A, B)
+    assert_parity(dtype, gpu_gemm(dtype, A, B), ref, D, f"{dtype} {M}x{N}x{K}")
+    assert_parity(dtype, gpu_gemm(dtype, A, B, workspace="auto"), ref, D, f"{dtype} {M}x{N}x{K} workspace")
 
 
 # ---------------------------------------------------------------- determinism and streams
@@ -961,9 +976,6 @@ def _to_kn(dtype, B):
     if dtype == "s4":
         return si.pack_s4(np.ascontiguousarray(oracle.s4_unpack(B).T))
     return np.ascontiguousarray(B.T)
-
-
-KSLICE = {"f16": 64, "s8": 128, "s4": 256}
 
 
 @pytest.mark.parametrize("dtype", ["f16", "s8", "s4"])
