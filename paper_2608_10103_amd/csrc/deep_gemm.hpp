@@ -150,9 +150,11 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_deep(const uint8_t 
     const long row0 = (long)tm * T::BM + wm * T::WTM;
     const long col0 = (long)tn * T::BN + wn * T::WTN + r;
     if constexpr (DT == S4)
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvShift8());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvShift8());
     else
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvSame());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvSame());
 }
 
 }  // namespace mpg

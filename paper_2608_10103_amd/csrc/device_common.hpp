@@ -186,6 +186,10 @@ __device__ __forceinline__ void epi_store_one(const EpiParams &e, void *C, long 
     store_out(e, C, i * N + j, epi_value<DT>(e, x, i, sb, zb, cs));
 }
 
+// What absent vectors are read from, so that every load of the terms is
+// issued at once, without a branch.
+static __device__ const int kEpiNone[1] = {0};
+
 // Calls f(integral_constant<int, I>) for I = 0 .. N-1, unrolled by
 // construction. The epilogue indexes the accumulator arrays only through
 // such compile-time indices: a loop the unroller declines (it does for the
@@ -200,13 +204,94 @@ __device__ __forceinline__ void static_for(F &&f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// A wave's MS x MS blocks (FM x FN of them): block (i, j) value v of lane
-// group h sits at row row0 + i MS + acc_row(h, v), column col0 + j MS (col0
-// includes the lane's column). conv maps an accumulator element to the raw
-// sum. Rows >= M and columns >= N are not stored.
-template <int DT, int MS, int FM, int FN, int NV, class AccT, class Conv>
-__device__ __forceinline__ void epi_store_tile(const EpiParams &e, void *C, const AccT (&acc)[FM][FN],
-                                               long row0, long col0, int h, int M, int N, Conv conv) {
+// Row and column terms of a tile's scaled outputs in LDS, at the start of the
+// (then free) copy buffers: per row scale, zero point and row sum of A; per
+// column scale, zero point and column sum of B less K times that zero point;
+// one flag per wave.
+template <int BM, int BN>
+struct EpiLds {
+    static constexpr int SA = 0, ZA = 4 * BM, RA = 8 * BM, SB = 12 * BM, ZB = SB + 4 * BN, CS = ZB + 4 * BN,
+                         FLAG = CS + 8 * BN;
+};
+
+// Loads them, each once, by all threads together (rows and columns past the
+// edge take the last one's). Returns, in every thread, whether a zero point
+// reaches 2^21 or a bracket 2^31 in magnitude (see epi_store_tile).
+template <int DT, int BM, int BN, int NT>
+__device__ __forceinline__ bool epi_terms(const EpiParams &e, uint8_t *lds, long row_t, long col_t, int M, int N) {
+    typedef EpiLds<BM, BN> L;
+    constexpr int ROUNDS = (BM + BN + NT - 1) / NT;
+    const auto beyond = [](int z) { return (int)((uint32_t)(z + (1 << 21)) >> 22); };
+    int scale[ROUNDS], zero[ROUNDS], sum[ROUNDS];
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        const int x = threadIdx.x + i * NT;
+        const bool row = x < BM;
+        const long at = row ? (row_t + x < M ? row_t + x : (long)M - 1)
+                            : (col_t + x - BM < N ? col_t + x - BM : (long)N - 1);
+        const auto load = [&](const void *a, const void *b) {
+            const void *p = row ? a : b;
+            return *(p ? reinterpret_cast<const int *>(p) + at : kEpiNone);
+        };
+        scale[i] = load(e.scale_a, e.scale_b);
+        if constexpr (DT != F16) {
+            zero[i] = load(e.zero_a, e.zero_b);
+            sum[i] = load(e.zero_b ? e.sum_a : nullptr, e.zero_a ? e.sum_b : nullptr);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every copy of every wave has landed
+    __syncthreads();
+    int big = 0;
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        const int x = threadIdx.x + i * NT;
+        if (ROUNDS * NT > BM + BN && x >= BM + BN) break;
+        const bool row = x < BM;
+        const int y = row ? x : x - BM;
+        *reinterpret_cast<int *>(lds + (row ? L::SA : L::SB) + 4 * y) =
+            (row ? e.scale_a : e.scale_b) ? scale[i] : __builtin_bit_cast(int, 1.0f);
+        if constexpr (DT != F16) {
+            *reinterpret_cast<int *>(lds + (row ? L::ZA : L::ZB) + 4 * y) = zero[i];
+            big |= beyond(zero[i]);
+            if (row) {
+                *reinterpret_cast<int *>(lds + L::RA + 4 * y) = sum[i];
+            } else {
+                const long long cs = e.zero_a ? (long long)sum[i] - (long long)e.K * zero[i] : 0;
+                *reinterpret_cast<long long *>(lds + L::CS + 8 * y) = cs;
+                big |= cs != (int)cs;
+            }
+        }
+    }
+    if constexpr (DT != F16) {
+        const bool any = __any(big);
+        if ((threadIdx.x & 63) == 0) *reinterpret_cast<int *>(lds + L::FLAG + 4 * (threadIdx.x >> 6)) = any;
+    }
+    __syncthreads();
+    int wide = 0;
+    if constexpr (DT != F16)
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) wide |= *reinterpret_cast<const int *>(lds + L::FLAG + 4 * w);
+    return __builtin_amdgcn_readfirstlane(wide) != 0;
+}
+
+// A wave's MS x MS blocks (FM x FN of them) of a workgroup's tile (row_t,
+// col_t): block (i, j) value v of lane group h sits at row row0 + i MS +
+// acc_row(h, v), column col0 + j MS (col0 includes the lane's column). conv
+// maps an accumulator element to the raw sum. Rows >= M and columns >= N are
+// not stored. Every thread of the workgroup calls it: scaled outputs take
+// their row and column terms from LDS, at `lds`, whose contents are spent.
+//
+// Scaled outputs: what bounds them is the latency of the terms (three vectors
+// over rows, three over columns): read from memory row by row, before each
+// row's stores, they took 20 of the 64 us of an INT8 2048 x 4096 x 4096 call
+// with zero points. Now each is loaded once per tile, by all threads together.
+// Zero points: sum ab - zb rowsum_a - za (colsum_b - K zb) in binary64, exact
+// while zero points are below 2^21 and the bracket below 2^31 (every product
+// is then below 2^52); tiles that hold larger ones use 64-bit integers.
+template <int DT, int MS, int FM, int FN, int NV, int BM, int BN, int NT, class AccT, class Conv>
+__device__ __forceinline__ void epi_store_tile(const EpiParams &e, void *C, const AccT (&acc)[FM][FN], uint8_t *lds,
+                                               long row_t, long col_t, long row0, long col0, int h, int M, int N,
+                                               Conv conv) {
     typedef typename Acc<DT, MS>::out out_t;
     if (e.out == OUT_PLAIN) {
         out_t *Co = reinterpret_cast<out_t *>(C);
@@ -220,26 +305,69 @@ __device__ __forceinline__ void epi_store_tile(const EpiParams &e, void *C, cons
         });
         return;
     }
+    typedef EpiLds<BM, BN> L;
+    const bool zp = DT != F16 && (e.zero_a || e.zero_b);
+    const bool terms = zp || e.scale_a || e.scale_b;
+    bool wide = false;
+    if (terms) wide = epi_terms<DT, BM, BN, NT>(e, lds, row_t, col_t, M, N);
+    const int lr = (int)(row0 - row_t), lc = (int)(col0 - col_t);
     float sb[FN];
-    long long zb[FN], cs[FN];
+    double zb[FN], cs[FN];
     static_for<FN>([&](auto j) __attribute__((always_inline)) {
-        const long col = col0 + j * MS;
-        const bool ok = col < N;
-        sb[j] = (e.scale_b && ok) ? e.scale_b[col] : 1.0f;
-        zb[j] = (e.zero_b && ok) ? e.zero_b[col] : 0;
-        cs[j] = (e.zero_a && ok) ? e.sum_b[col] : 0;
+        const int c = lc + j * MS;
+        sb[j] = terms ? *reinterpret_cast<const float *>(lds + L::SB + 4 * c) : 1.0f;
+        zb[j] = zp ? (double)*reinterpret_cast<const int *>(lds + L::ZB + 4 * c) : 0.0;
+        cs[j] = zp ? (double)(int)*reinterpret_cast<const long long *>(lds + L::CS + 8 * c) : 0.0;
     });
     static_for<FM>([&](auto i) __attribute__((always_inline)) {
-        static_for<NV>([&](auto v) __attribute__((always_inline)) {
-            const long row = row0 + i * MS + acc_row<MS>(h, v);
-            if (row < M) {
-                static_for<FN>([&](auto j) __attribute__((always_inline)) {
-                    const long col = col0 + j * MS;
-                    if (col < N)
-                        store_out(e, C, row * N + col,
-                                  epi_value<DT>(e, conv(acc[i][j][v.value]), row, sb[j], zb[j], cs[j]));
+        static_for<NV / 4>([&](auto g) __attribute__((always_inline)) {
+            // four consecutive rows
+            const int r0 = lr + i * MS + acc_row<MS>(h, g * 4);
+            f32x4 sa = {1.0f, 1.0f, 1.0f, 1.0f};
+            i32x4 za = {0, 0, 0, 0}, ra = {0, 0, 0, 0};
+            if (terms) sa = *reinterpret_cast<const f32x4 *>(lds + L::SA + 4 * r0);
+            if (zp) {
+                za = *reinterpret_cast<const i32x4 *>(lds + L::ZA + 4 * r0);
+                ra = *reinterpret_cast<const i32x4 *>(lds + L::RA + 4 * r0);
+            }
+            float x[4][FN];
+            const auto each = [&](auto f) __attribute__((always_inline)) {
+                static_for<4>([&](auto u) __attribute__((always_inline)) {
+                    static_for<FN>([&](auto j) __attribute__((always_inline)) {
+                        f(u, j, conv(acc[i][j][g * 4 + u]));
+                    });
+                });
+            };
+            if (!zp) {
+                each([&](auto u, auto j, auto c) __attribute__((always_inline)) { x[u][j] = (float)c; });
+            } else if (!wide) {
+                each([&](auto u, auto j, auto c) __attribute__((always_inline)) {
+                    x[u][j] = (float)fma(-(double)za[u.value], cs[j], fma(-zb[j], (double)ra[u.value], (double)c));
+                });
+            } else if constexpr (DT != F16) {
+                each([&](auto u, auto j, auto c) __attribute__((always_inline)) {
+                    const int y = lc + j * MS;
+                    const long long z = *reinterpret_cast<const int *>(lds + L::ZB + 4 * y);
+                    x[u][j] = (float)((long long)c - z * ra[u.value] -
+                                      za[u.value] * *reinterpret_cast<const long long *>(lds + L::CS + 8 * y));
                 });
             }
+            const auto store = [&](auto put) __attribute__((always_inline)) {
+                static_for<4>([&](auto u) __attribute__((always_inline)) {
+                    const long row = row0 + i * MS + acc_row<MS>(h, g * 4 + u);
+                    if (row < M)
+                        static_for<FN>([&](auto j) __attribute__((always_inline)) {
+                            const long col = col0 + j * MS;
+                            if (col < N) put(row * N + col, x[u][j] * sa[u.value] * sb[j]);
+                        });
+                });
+            };
+            if (e.out == OUT_F32)
+                store([&](long at, float y) __attribute__((always_inline)) { reinterpret_cast<float *>(C)[at] = y; });
+            else if (e.out == OUT_F16)
+                store([&](long at, float y) __attribute__((always_inline)) { reinterpret_cast<_Float16 *>(C)[at] = (_Float16)y; });
+            else
+                store([&](long at, float y) __attribute__((always_inline)) { reinterpret_cast<uint16_t *>(C)[at] = f32_to_bf16_rne(y); });
         });
     });
 }
@@ -255,25 +383,46 @@ struct ConvToInt {  // INT4 on the FP6 MFMA: exact integers held in FP32
     __device__ __forceinline__ int operator()(float x) const { return (int)x; }
 };
 
-// Row sums of an integer operand stored as R rows of K values (int8 bytes or
-// packed INT4 nibbles), one block per row; used by the zero-point terms.
+// 16 bytes at any address: global loads need no alignment.
+typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// Row sums of the integer operands (rows of Kb int8 bytes or packed INT4
+// bytes) for the zero-point terms: RA rows of A, then RB rows of B (either may
+// be none), a wave per row, 1 KiB of it per load and dot products with ones.
+// Bound by reading the operands once: 16 MiB of B (4096 rows of 4096) 12.7 ->
+// 5 us against one block per row that read a byte per lane.
+constexpr int ROW_SUMS_WAVES = 4;
 template <int DT>
-__global__ __launch_bounds__(256) void row_sums(const uint8_t *__restrict__ X, int R, int K,
-                                                int *__restrict__ out) {
-    __shared__ int part[4];
-    const long kb = row_bytes(DT, K);
-    const uint8_t *row = X + (size_t)blockIdx.x * kb;
+__global__ __launch_bounds__(64 * ROW_SUMS_WAVES) void row_sums(const uint8_t *__restrict__ A, long RA,
+                                                                int *__restrict__ out_a,
+                                                                const uint8_t *__restrict__ B, long RB,
+                                                                int *__restrict__ out_b, long Kb) {
+    const int lane = threadIdx.x & 63;
+    long r = (long)blockIdx.x * ROW_SUMS_WAVES + (threadIdx.x >> 6);
+    if (r >= RA + RB) return;
+    const uint8_t *row = r < RA ? A + (size_t)r * Kb : B + (size_t)(r - RA) * Kb;
     int s = 0;
-    for (long b = threadIdx.x; b < kb; b += 256) {
-        const uint32_t byte = row[b];
-        if constexpr (DT == S8) s += (int)(int8_t)byte;
-        else s += s4_nibble(byte, 0) + s4_nibble(byte, 1);
+    const auto add = [&](uint32_t x) __attribute__((always_inline)) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        if constexpr (DT == S8) s = __builtin_amdgcn_sdot4((int)x, 0x01010101, s, false);
+        else s = __builtin_amdgcn_sdot8((int)x, 0x11111111, s, false);
+#endif
+    };
+#pragma unroll 4
+    for (long o = lane * 16; o + 16 <= Kb; o += 1024) {
+        const i32x4 x = *reinterpret_cast<const i32x4_any *>(row + o);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) add((uint32_t)x[d]);
     }
+    // the last Kb % 16 bytes, one per lane
+    const long o = (Kb & ~15L) + lane;
+    if (o < Kb) add(row[o]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) out[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+    if (lane == 0) {
+        if (r < RA) out_a[r] = s;
+        else out_b[r - RA] = s;
+    }
 }
 
 // Rank of workgroup `id` of `n` in an order where each XCD owns a

@@ -408,7 +408,8 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void f6_gemm(const uint8_t *__restr
     const long row0 = (long)tm * T::BM + wm * T::WTM;
     const long col0 = (long)tn * T::BN + wn * T::WTN + r;
     // the sums are integers of magnitude <= 2^24: the conversion is exact
-    epi_store_tile<S4, 32, T::FM, T::FN, 16>(epi, C, acc, row0, col0, h, M, N, ConvToInt());
+    epi_store_tile<S4, 32, T::FM, T::FN, 16, T::BM, T::BN, T::NTHREADS>(epi, C, acc, lds, (long)tm * T::BM, (long)tn * T::BN,
+                                                                          row0, col0, h, M, N, ConvToInt());
 }
 
 }  // namespace mpg

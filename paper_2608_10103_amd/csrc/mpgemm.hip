@@ -946,24 +946,17 @@ hipError_t zero_point_sums(int dtype, int M, int N, int K, const void *A, const 
     if (!epi.zero_a && !epi.zero_b) return hipSuccess;
     const void *fn = dtype == S8 ? reinterpret_cast<const void *>(&row_sums<S8>)
                                  : reinterpret_cast<const void *>(&row_sums<S4>);
-    if (epi.zero_b) {  // needs the row sums of A
-        const uint8_t *x = static_cast<const uint8_t *>(A);
-        int r = M, k = K;
-        int *out = sums;
-        void *args[] = {&x, &r, &k, &out};
-        const hipError_t e = hipLaunchKernel(fn, dim3(M), dim3(256), args, 0, stream);
-        if (e != hipSuccess) return e;
-        epi.sum_a = out;
-    }
-    if (epi.zero_a) {  // needs the column sums of B (rows of its N x K storage)
-        const uint8_t *x = static_cast<const uint8_t *>(B);
-        int r = N, k = K;
-        int *out = sums + M;
-        void *args[] = {&x, &r, &k, &out};
-        const hipError_t e = hipLaunchKernel(fn, dim3(N), dim3(256), args, 0, stream);
-        if (e != hipSuccess) return e;
-        epi.sum_b = out;
-    }
+    // zero_b needs the row sums of A, zero_a the column sums of B (rows of its
+    // N x K storage)
+    const uint8_t *a = static_cast<const uint8_t *>(A), *b = static_cast<const uint8_t *>(B);
+    long ra = epi.zero_b ? M : 0, rb = epi.zero_a ? N : 0, kb = row_bytes(dtype, K);
+    int *out_a = sums, *out_b = sums + M;
+    void *args[] = {&a, &ra, &out_a, &b, &rb, &out_b, &kb};
+    const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)((ra + rb + ROW_SUMS_WAVES - 1) / ROW_SUMS_WAVES)),
+                                         dim3(64 * ROW_SUMS_WAVES), args, 0, stream);
+    if (e != hipSuccess) return e;
+    if (epi.zero_b) epi.sum_a = out_a;
+    if (epi.zero_a) epi.sum_b = out_b;
     return hipSuccess;
 }
 

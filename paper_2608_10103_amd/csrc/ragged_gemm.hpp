@@ -104,7 +104,7 @@ __global__ __launch_bounds__(T::NTHREADS, 2) void ragged_gemm(const uint8_t *__r
         __syncthreads();
         compute_stage<DT, T>(lds, wm, wn, r, h, acc);
     }
-    pf_store<DT, T>(epi, Cv, acc, tm, tn, M, N);
+    pf_store<DT, T>(epi, Cv, acc, tm, tn, M, N, lds);
 }
 
 }  // namespace mpg

@@ -172,7 +172,7 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_sk(const uint8_t *_
             acc, sk.counters + wk.t, sk.partials + (size_t)(wk.u - wk.part) * T::BM * T::BN, wk.part, sk.parts,
             reinterpret_cast<int *>(lds)))
         return;
-    pf_store<DT, T>(epi, Cv, acc, tm, tn, M, N);
+    pf_store<DT, T>(epi, Cv, acc, tm, tn, M, N, lds);
 }
 
 // Stream-K schedule of the one-wave-per-SIMD kernel (wide_gemm): 256 x 256
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(WideCfg::NTHREADS, 1) void wide_gemm_sk(const uint8
             acc, sk.counters + wk.t, sk.partials + (size_t)(wk.u - wk.part) * WideCfg::BM * WideCfg::BN, wk.part,
             sk.parts, reinterpret_cast<int *>(lds)))
         return;
-    wide_store<DT, PLAIN>(epi, Cv, acc, tm, tn, M, N);
+    wide_store<DT, PLAIN>(epi, Cv, acc, tm, tn, M, N, lds);
 }
 
 // Stream-K schedule of the one-wave-per-SIMD FP6 kernel (wide_f6_gemm,
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(WideF6Cfg::NTHREADS, 1) void wide_f6_gemm_sk(
             acc, sk.counters + wk.t, sk.partials + (size_t)(wk.u - wk.part) * WideF6Cfg::BM * WideF6Cfg::BN,
             wk.part, sk.parts, reinterpret_cast<int *>(lds)))
         return;
-    wf6_store<PLAIN>(epi, C, acc, tm, tn, M, N);
+    wf6_store<PLAIN>(epi, C, acc, tm, tn, M, N, lds);
 }
 
 }  // namespace mpg

@@ -464,7 +464,7 @@ __device__ __forceinline__ void pf_accumulate(uint8_t *lds, const uint8_t *A, co
 template <int DT, class T>
 __device__ __forceinline__ void pf_store(const EpiParams &epi, void *Cv,
                                          const typename Acc<DT, T::MS>::type (&acc)[T::FM][T::FN], int tm,
-                                         int tn, int M, int N) {
+                                         int tn, int M, int N, uint8_t *lds) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int r = lane % T::MS, h = lane / T::MS;
@@ -472,9 +472,11 @@ __device__ __forceinline__ void pf_store(const EpiParams &epi, void *Cv,
     const long row0 = (long)tm * T::BM + wm * T::WTM;
     const long col0 = (long)tn * T::BN + wn * T::WTN + r;
     if constexpr (DT == S4)
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvShift8());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvShift8());
     else
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvSame());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvSame());
 }
 
 //
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_pf(const uint8_t *_
 
     if (splits > 1 && !splitk_fixup<DT, T>(acc, pid, split, splits, counters, partials, lds))
         return;
-    pf_store<DT, T>(epi, Cv, acc, tm, tn, M, N);
+    pf_store<DT, T>(epi, Cv, acc, tm, tn, M, N, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -527,9 +529,6 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_pf(const uint8_t *_
 // arithmetic near the end of K is clamped instead of branched (the surplus
 // loads re-read the last slice, the surplus writes land in a buffer no one
 // reads again), so every slice body is one scheduling region.
-
-// 16 bytes at any address: global loads need no alignment.
-typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 
 template <class T, int J0, int J1>
 __device__ __forceinline__ void gload_part(i32x4 (&reg)[T::DMA_PER_WAVE], const uint8_t *const *src,
@@ -708,9 +707,11 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_rs(const uint8_t *_
     const long row0 = (long)tm * T::BM + wm * T::WTM;
     const long col0 = (long)tn * T::BN + wn * T::WTN + r;
     if constexpr (DT == S4)
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvShift8());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvShift8());
     else
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvSame());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvSame());
 }
 
 // ---------------------------------------------------------------------------
@@ -892,9 +893,11 @@ __global__ __launch_bounds__(512, 1) void tiled_gemm_pp(const uint8_t *__restric
     const long row0 = (long)tm * T::BM + g * T::WTM;
     const long col0 = (long)tn * T::BN + w4 * T::WTN + r;
     if constexpr (DT == S4)
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvShift8());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvShift8());
     else
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvSame());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvSame());
 }
 
 template <int DT, class T>
@@ -943,9 +946,11 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm(const uint8_t *__re
     const long row0 = (long)tm * T::BM + wm * T::WTM;
     const long col0 = (long)tn * T::BN + wn * T::WTN + r;
     if constexpr (DT == S4)
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvShift8());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvShift8());
     else
-        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, h, M, N, ConvSame());
+        epi_store_tile<DT, T::MS, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, h, M, N, ConvSame());
 }
 
 }  // namespace mpg

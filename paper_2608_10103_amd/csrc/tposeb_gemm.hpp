@@ -296,9 +296,11 @@ __global__ __launch_bounds__(T::NTHREADS, 1) void tiled_gemm_tb(const uint8_t *_
     const long row0 = (long)tm * T::BM + wm * T::WTM;
     const long col0 = (long)tn * T::BN + wn * T::WTN + (lane % 32);
     if constexpr (DT == S4)  // INT4 sums are carried times 256 (s4_lo_x16)
-        epi_store_tile<DT, 32, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, lane / 32, M, N, ConvShift8());
+        epi_store_tile<DT, 32, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, lane / 32, M, N, ConvShift8());
     else
-        epi_store_tile<DT, 32, T::FM, T::FN, T::NV>(epi, Cv, acc, row0, col0, lane / 32, M, N, ConvSame());
+        epi_store_tile<DT, 32, T::FM, T::FN, T::NV, T::BM, T::BN, T::NTHREADS>(
+            epi, Cv, acc, lds, (long)tm * T::BM, (long)tn * T::BN, row0, col0, lane / 32, M, N, ConvSame());
 }
 
 }  // namespace mpg

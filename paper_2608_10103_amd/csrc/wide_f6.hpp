@@ -200,7 +200,7 @@ __device__ __forceinline__ void wf6_accumulate(uint8_t *lds, const uint8_t *Ap, 
 // (ragged edges, scales).
 template <bool PLAIN>
 __device__ __forceinline__ void wf6_store(const EpiParams &epi, int32_t *C, const f32x16 (&acc)[4][4], int tm,
-                                          int tn, int M, int N) {
+                                          int tn, int M, int N, uint8_t *lds) {
     typedef WideF6Cfg T;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 31, h = lane >> 5;
@@ -220,7 +220,9 @@ __device__ __forceinline__ void wf6_store(const EpiParams &epi, int32_t *C, cons
                 for (int j = 0; j < 4; ++j) rowp[32 * j] = (int)acc[i][j][v];
             }
     } else {
-        epi_store_tile<S4, 32, 4, 4, 16>(epi, C, acc, row0, col0, h, M, N, ConvToInt());
+        epi_store_tile<S4, 32, 4, 4, 16, T::BM, T::BN, T::NTHREADS>(epi, C, acc, lds, (long)tm * T::BM,
+                                                                     (long)tn * T::BN, row0, col0, h, M, N,
+                                                                     ConvToInt());
     }
 }
 
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(WideF6Cfg::NTHREADS, 1) void wide_f6_gemm(
     tile_coords(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, 4, tm, tn);
     f32x16 acc[4][4];
     wf6_accumulate<AUX>(lds, Ap, Aq, Bp, Bq, Ma, Nb, KT, tm, tn, 0, KT, acc);
-    wf6_store<PLAIN>(epi, C, acc, tm, tn, M, N);
+    wf6_store<PLAIN>(epi, C, acc, tm, tn, M, N, lds);
 }
 
 }  // namespace mpg

@@ -226,7 +226,7 @@ __device__ __forceinline__ void wide_accumulate(uint8_t *lds, const uint8_t *A, 
 template <int DT, bool PLAIN>
 __device__ __forceinline__ void wide_store(const EpiParams &epi, void *Cv,
                                            const typename Acc<DT, 16>::type (&acc)[8][8], int tm, int tn,
-                                           int M, int N) {
+                                           int M, int N, uint8_t *lds) {
     typedef WideCfg T;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane % 16, h = lane / 16;
@@ -247,7 +247,8 @@ __device__ __forceinline__ void wide_store(const EpiParams &epi, void *Cv,
                 for (int j = 0; j < 8; ++j) rowp[16 * j] = acc[i][j][v];
             }
     } else {
-        epi_store_tile<DT, 16, 8, 8, 4>(epi, Cv, acc, row0, col0, h, M, N, ConvSame());
+        epi_store_tile<DT, 16, 8, 8, 4, T::BM, T::BN, T::NTHREADS>(epi, Cv, acc, lds, (long)tm * T::BM,
+                                                                    (long)tn * T::BN, row0, col0, h, M, N, ConvSame());
     }
 }
 
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(WideCfg::NTHREADS, 1) void wide_gemm(const uint8_t 
     tile_coords(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, 4, tm, tn);
     typename Acc<DT, 16>::type acc[8][8];
     wide_accumulate<DT, AUX>(lds, A, B, M, N, Kb, tm, tn, 0, Kb / WideCfg::BKB, acc);
-    wide_store<DT, PLAIN>(epi, Cv, acc, tm, tn, M, N);
+    wide_store<DT, PLAIN>(epi, Cv, acc, tm, tn, M, N, lds);
 }
 
 }  // namespace mpg

@@ -344,7 +344,9 @@ __global__ __launch_bounds__(WideI4Cfg::NTHREADS, 1) void wide_i4_gemm(const uin
                 for (int j = 0; j < 4; ++j) rowp[32 * j] = (int)acc[i][j][v];
             }
     } else {
-        epi_store_tile<S4, 32, 4, 4, 16>(epi, Cv, acc, row0, col0, h, M, N, ConvToInt());
+        epi_store_tile<S4, 32, 4, 4, 16, T::BM, T::BN, T::NTHREADS>(epi, Cv, acc, lds, (long)tm * T::BM,
+                                                                     (long)tn * T::BN, row0, col0, h, M, N,
+                                                                     ConvToInt());
     }
 }
 

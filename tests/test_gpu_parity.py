@@ -918,6 +918,24 @@ def test_scaled_epilogue_every_kernel(dtype):
     _log(f"{dtype} scaled epilogue, every variant: ok")
 
 
+# Zero points around 2^21 (where the epilogue leaves binary64 for 64-bit
+# integers) in a few rows and columns only, so some tiles hold one and others
+# none; rows of the operands off every load width of the row sums.
+@pytest.mark.parametrize("dtype", ["s8", "s4"])
+@pytest.mark.parametrize("K", [14, 34, 130, 256, 1026, 2304])
+@pytest.mark.parametrize("sides", ["a", "b", "ab"])
+def test_zero_points_of_any_size_and_row_length(dtype, K, sides):
+    M, N = 150, 333
+    A, B = si.gen_operands(dtype, M, N, K, seed=K)
+    sa, sb, za, zb = _scales(dtype, M, N, K + 1, True)
+    za[[0, 70, 149]] = (1 << 21) - 1, -(1 << 21), 1 << 26
+    zb[[1, 200]] = -(1 << 25), 1 << 21
+    za, zb = za if "a" in sides else None, zb if "b" in sides else None
+    C = _run_scaled(dtype, A, B, "f32", sa, sb, za, zb)
+    _, exact, D = oracle.gemm_scaled(dtype, A, B, "f32", sa, sb, za, zb)
+    assert_scaled(C, exact, D, "f32", f"{dtype} {M}x{N}x{K} zero points {sides}")
+
+
 @pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("out", OUTS)
 def test_scaled_entry_point(dtype, out):
