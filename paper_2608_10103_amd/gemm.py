@@ -100,21 +100,45 @@ EXPORTED_SYMBOLS = ("gemm_f16_f32", "gemm_s8_s32", "gemm_s4_s32", "gemm_scaled",
                     "mpgemm_s4_run_to_e2m3", "mpgemm_gemm_bt", "mpgemm_sk_schedule")
 
 
+# The current stream's handle without building a torch.cuda.Stream for it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream, device) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(device.index)
         stream = torch.cuda.current_stream(device)
     return int(stream.cuda_stream)
 
 
+def _on_device(device, fn, *args):
+    """fn(*args) with `device` current; most calls find it so, and entering
+    and leaving torch's device context costs as much as a third of a launch."""
+    if torch.cuda.current_device() == device.index:
+        return fn(*args)
+    with torch.cuda.device(device):
+        return fn(*args)
+
+
+def _operand_error(name, t, want):
+    if not isinstance(t, torch.Tensor) or t.dtype != want or t.dim() != 2:
+        raise TypeError(f"{name} must be a 2-D {want} tensor")
+    if not t.is_cuda:
+        raise ValueError(f"{name} must be on a GPU")
+    raise ValueError(f"{name} must be contiguous")
+
+
+def _good(t, want) -> bool:
+    return isinstance(t, torch.Tensor) and t.dtype == want and t.dim() == 2 and t.is_cuda and t.is_contiguous()
+
+
 def _shapes(dtype: str, A: torch.Tensor, B: torch.Tensor):
     want = _IN_DTYPE[dtype]
-    for name, t in (("A", A), ("B", B)):
-        if not isinstance(t, torch.Tensor) or t.dtype != want or t.dim() != 2:
-            raise TypeError(f"{name} must be a 2-D {want} tensor")
-        if not t.is_cuda:
-            raise ValueError(f"{name} must be on a GPU")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
+    if not _good(A, want):
+        _operand_error("A", A, want)
+    if not _good(B, want):
+        _operand_error("B", B, want)
     if A.device != B.device:
         raise ValueError("A and B must be on the same device")
     M, KA = A.shape
@@ -128,7 +152,7 @@ def _shapes(dtype: str, A: torch.Tensor, B: torch.Tensor):
 def _out(dtype, M, N, A, C):
     if C is None:
         return torch.empty((M, N), dtype=_OUT_DTYPE[dtype], device=A.device)
-    if C.dtype != _OUT_DTYPE[dtype] or tuple(C.shape) != (M, N) or not C.is_contiguous():
+    if C.dtype != _OUT_DTYPE[dtype] or C.shape != (M, N) or not C.is_contiguous():
         raise ValueError(f"C must be a contiguous ({M}, {N}) {_OUT_DTYPE[dtype]} tensor")
     if C.device != A.device:
         raise ValueError("C must be on the operands' device")
@@ -182,21 +206,18 @@ def _call(dtype: str, A, B, C, stream, variant, splits=None, workspace=None):
     if splits is not None and variant is None:
         raise ValueError("splits needs an explicit variant")
     wp, wn, _keep = _workspace(workspace, dtype, M, N, K, variant, splits, None, A.device, stream)
-    with torch.cuda.device(A.device):
-        if wn == 0 and splits is None:
-            if variant is None:
-                fn = getattr(lib(), {"f16": "gemm_f16_f32", "s8": "gemm_s8_s32",
-                                     "s4": "gemm_s4_s32"}[dtype])
-                code = fn(M, N, K, A.data_ptr(), B.data_ptr(), C.data_ptr(), s)
-            else:
-                code = lib().mpgemm_run_variant(DTYPE_CODE[dtype], variant, M, N, K, A.data_ptr(),
-                                                B.data_ptr(), C.data_ptr(), s)
-        elif variant is None:
-            code = lib().mpgemm_gemm_ws(DTYPE_CODE[dtype], M, N, K, A.data_ptr(), B.data_ptr(), C.data_ptr(),
-                                        None, wp, wn, s)
+    L, d, dev = lib(), DTYPE_CODE[dtype], A.device
+    a, b, c = A.data_ptr(), B.data_ptr(), C.data_ptr()
+    if wn == 0 and splits is None:
+        if variant is None:
+            fn = (L.gemm_f16_f32, L.gemm_s8_s32, L.gemm_s4_s32)[d]
+            code = _on_device(dev, fn, M, N, K, a, b, c, s)
         else:
-            code = lib().mpgemm_run_variant_ws(DTYPE_CODE[dtype], variant, splits or 0, M, N, K, A.data_ptr(),
-                                               B.data_ptr(), C.data_ptr(), None, wp, wn, s)
+            code = _on_device(dev, L.mpgemm_run_variant, d, variant, M, N, K, a, b, c, s)
+    elif variant is None:
+        code = _on_device(dev, L.mpgemm_gemm_ws, d, M, N, K, a, b, c, None, wp, wn, s)
+    else:
+        code = _on_device(dev, L.mpgemm_run_variant_ws, d, variant, splits or 0, M, N, K, a, b, c, None, wp, wn, s)
     if code != 0:
         raise HipError(code, f"{dtype} GEMM {M}x{N}x{K}")
     return C
@@ -230,9 +251,9 @@ def gemm_bt(dtype: str, A, B_kn, C=None, stream=None):
         raise ValueError("transposed B: f16, s8 or s4")
     want = _IN_DTYPE[dtype]
     for name, t in (("A", A), ("B", B_kn)):
-        if not isinstance(t, torch.Tensor) or t.dtype != want or t.dim() != 2:
-            raise TypeError(f"{name} must be a 2-D {want} tensor")
-        if not t.is_cuda or not t.is_contiguous():
+        if not _good(t, want):
+            if not isinstance(t, torch.Tensor) or t.dtype != want or t.dim() != 2:
+                raise TypeError(f"{name} must be a 2-D {want} tensor")
             raise ValueError(f"{name} must be a contiguous GPU tensor")
     if A.device != B_kn.device:
         raise ValueError("A and B must be on the same device")
@@ -244,9 +265,8 @@ def gemm_bt(dtype: str, A, B_kn, C=None, stream=None):
         raise ValueError(f"K mismatch: A has {K}, B has {KB} rows")
     C = _out(dtype, M, N, A, C)
     s = _stream_ptr(stream, A.device)
-    with torch.cuda.device(A.device):
-        code = lib().mpgemm_gemm_bt(DTYPE_CODE[dtype], M, N, K, A.data_ptr(), B_kn.data_ptr(),
-                                    C.data_ptr(), s)
+    code = _on_device(A.device, lib().mpgemm_gemm_bt, DTYPE_CODE[dtype], M, N, K, A.data_ptr(), B_kn.data_ptr(),
+                      C.data_ptr(), s)
     if code != 0:
         raise HipError(code, f"transposed-B {dtype} GEMM {M}x{N}x{K}")
     return C
@@ -285,23 +305,20 @@ def gemm_scaled(dtype: str, A, B, scale_a=None, scale_b=None, zero_a=None, zero_
                    OUT_TYPE[out_dtype])
     if C is None:
         C = torch.empty((M, N), dtype=out_dtype, device=dev)
-    elif C.dtype != out_dtype or tuple(C.shape) != (M, N) or not C.is_contiguous() or C.device != dev:
+    elif C.dtype != out_dtype or C.shape != (M, N) or not C.is_contiguous() or C.device != dev:
         raise ValueError(f"C must be a contiguous ({M}, {N}) {out_dtype} tensor on {dev}")
     if splits is not None and variant is None:
         raise ValueError("splits needs an explicit variant")
     wp, wn, _keep = _workspace(workspace, dtype, M, N, K, variant, splits, epi, dev, stream)
     s = _stream_ptr(stream, dev)
-    with torch.cuda.device(dev):
-        if variant is None and wn == 0:
-            code = lib().gemm_scaled(DTYPE_CODE[dtype], M, N, K, A.data_ptr(), B.data_ptr(), C.data_ptr(),
-                                     ctypes.addressof(epi), s)
-        elif variant is None:
-            code = lib().mpgemm_gemm_ws(DTYPE_CODE[dtype], M, N, K, A.data_ptr(), B.data_ptr(), C.data_ptr(),
-                                        ctypes.addressof(epi), wp, wn, s)
-        else:
-            code = lib().mpgemm_run_variant_ws(DTYPE_CODE[dtype], variant, splits or 0, M, N, K,
-                                               A.data_ptr(), B.data_ptr(), C.data_ptr(),
-                                               ctypes.addressof(epi), wp, wn, s)
+    L, d, ep = lib(), DTYPE_CODE[dtype], ctypes.addressof(epi)
+    a, b, c = A.data_ptr(), B.data_ptr(), C.data_ptr()
+    if variant is None and wn == 0:
+        code = _on_device(dev, L.gemm_scaled, d, M, N, K, a, b, c, ep, s)
+    elif variant is None:
+        code = _on_device(dev, L.mpgemm_gemm_ws, d, M, N, K, a, b, c, ep, wp, wn, s)
+    else:
+        code = _on_device(dev, L.mpgemm_run_variant_ws, d, variant, splits or 0, M, N, K, a, b, c, ep, wp, wn, s)
     if code != 0:
         raise HipError(code, f"scaled {dtype} GEMM {M}x{N}x{K}")
     return C
