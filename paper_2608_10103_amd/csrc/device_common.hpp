@@ -190,6 +190,46 @@ __device__ __forceinline__ void epi_store_one(const EpiParams &e, void *C, long 
 // issued at once, without a branch.
 static __device__ const int kEpiNone[1] = {0};
 
+// The same for kernels that know an element's place early: its terms are
+// loaded (past the edge: the last row's and column's) long before its sum is
+// there, and first looked at when it is stored.
+struct EpiOne {
+    int sa, sb, za, zb, ra, cs;
+};
+template <int DT>
+__device__ __forceinline__ EpiOne epi_one_terms(const EpiParams &e, long i, long j, int M, int N) {
+    EpiOne t{0, 0, 0, 0, 0, 0};
+    if (e.out == OUT_PLAIN) return t;
+    i = i < M ? i : (long)M - 1;
+    j = j < N ? j : (long)N - 1;
+    const auto load = [](const void *p, long at) { return *(p ? reinterpret_cast<const int *>(p) + at : kEpiNone); };
+    t.sa = load(e.scale_a, i);
+    t.sb = load(e.scale_b, j);
+    if constexpr (DT != F16) {
+        t.za = load(e.zero_a, i);
+        t.zb = load(e.zero_b, j);
+        t.ra = load(e.zero_b ? e.sum_a : nullptr, i);
+        t.cs = load(e.zero_a ? e.sum_b : nullptr, j);
+    }
+    return t;
+}
+template <int DT, class V>
+__device__ __forceinline__ void epi_store_terms(const EpiParams &e, const EpiOne &t, void *C, long i, long j, long N,
+                                                V x) {
+    if (e.out == OUT_PLAIN) {
+        reinterpret_cast<V *>(C)[i * N + j] = x;
+        return;
+    }
+    float v;
+    if constexpr (DT == F16)
+        v = x;
+    else
+        v = (float)((long long)x - (long long)t.zb * t.ra - (long long)t.za * t.cs + (long long)e.K * t.za * t.zb);
+    const float sa = e.scale_a ? __builtin_bit_cast(float, t.sa) : 1.0f;
+    const float sb = e.scale_b ? __builtin_bit_cast(float, t.sb) : 1.0f;
+    store_out(e, C, i * N + j, v * sa * sb);
+}
+
 // Calls f(integral_constant<int, I>) for I = 0 .. N-1, unrolled by
 // construction. The epilogue indexes the accumulator arrays only through
 // such compile-time indices: a loop the unroller declines (it does for the

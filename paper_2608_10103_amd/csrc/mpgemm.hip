@@ -288,9 +288,11 @@ constexpr int kNumNarrowW = 3;
 constexpr int V_DEEP = 59;          // spread32x64_w1x2_k128_s8_m16
 constexpr int kNumDeep = 5;
 // Small tiles (refine), never split: 16 x 16 and 32 x 32 with an eight-slice
-// ring, 32 x 32 with four slices, 64 x 64 with eight waves and five.
+// ring, 32 x 32 with four slices, 64 x 64 with eight waves and five; 16 x 16
+// with K split over two and four waves.
 constexpr int V_SMALL = V_DEEP + kNumDeep;  // spread16x16_w1x1_k128_s8_m16
-constexpr int kNumSmall = 4;
+constexpr int V_KSPLIT = V_SMALL + 4;       // deep16x16_k128_s8_w2
+constexpr int kNumSmall = 6;
 
 // Problems the narrow tiles serve: at most 1024 rows on the small side and
 // at least 1024 on the large one, with the small side at most 512 rows or
@@ -696,6 +698,8 @@ const SliceCost kSliceCost[] = {
     {V_SMALL + 1, 2, .130, .115, .305, .220},    // 32 x 32, four waves, eight slices
     {V_SMALL + 2, 4, .165, .105, .300, .184},    // 32 x 32, four waves, four slices
     {V_SMALL + 3, 2, .235, .260, .400, .516},    // 64 x 64, eight waves, five slices
+    {V_KSPLIT, 2, .058, .043, .125, .063},       // 16 x 16, K over two waves, over four
+    {V_KSPLIT + 1, 1, .046, .046, .095, .095},   // (a slice of the whole K)
     {V_NARROW, 3, .235, .250, .420, .540},       // 32 x 64; 32 x 128; mirrors
     {V_NARROW + 1, 2, .290, .300, .500, .500},
     {V_NARROW + 3, 3, .235, .250, .420, .540},
@@ -713,7 +717,9 @@ const SliceCost kSliceCost[] = {
     {V_SPREAD128_K128, 1, .450, .600, .800, .800},
     {V_PIPE64, 2, .750, .750, .750, .750},
 };
-constexpr double kLaunchUs = 2.2, kSplitUs = 6.0;  // launch and end; the split's fix-up
+// launch and end; a split's fix-up, over the workspace and over a workgroup's
+// waves; what memory delivers to these kernels (bytes per us)
+constexpr double kLaunchUs = 2.2, kSplitUs = 6.0, kWaveSplitUs = 0.4, kMemoryRate = 5.5e6;
 
 // Modelled time of a variant in kSliceCost, or -1.
 double tile_us(int dtype, int variant, int splits, int M, int N, int K) {
@@ -726,30 +732,39 @@ double tile_us(int dtype, int variant, int splits, int M, int N, int K) {
         const auto per_slice = [&](long n) { return alone > n * shared ? alone : n * shared; };
         double t = (double)(wgs / round) * per_slice(c.resident);
         if (wgs % round) t += per_slice((wgs % round + 255) / 256);
-        return kLaunchUs + slices * t + (splits > 1 ? kSplitUs + splits - 1 : 0.0);
+        return kLaunchUs + slices * t + (splits > 1 ? kSplitUs + splits - 1 : 0.0) +
+               (variant >= V_KSPLIT && variant < V_SMALL + kNumSmall ? kWaveSplitUs : 0.0);
     }
     return -1;
 }
 
 // Modelled time of a streaming kernel: K-steps of a wave (whole prefetch
-// groups) times the workgroups of a CU; the small operand's rows, read from
-// L2 by every wave, cost up to half as much again.
+// groups) times the workgroups of a CU (two side by side take 1.5 times as
+// long for INT4, whose steps wait for the decode, 1.85 for the others); the
+// small operand's rows, read from L2 by every wave, cost up to half as much
+// again.
 double skinny_us(int dtype, int variant, int M, int N, int K) {
     const Variant &v = table(dtype)[variant];
     const int small = M < N ? M : N, large = M < N ? N : M, group = variant == V_SKINNY16_D8 ? 8 : 4;
     const long steps = (row_bytes(dtype, K) / 64 + SKINNY_WAVES - 1) / SKINNY_WAVES;
     const long wgs = (large + v.bn - 1) / v.bn;
     const double step = v.bm > 16 ? 1.5 : (v.bn > 16 ? .55 : (dtype == S4 ? .43 : .33)) + .2 * small / 16;
-    return kLaunchUs + (double)((steps + group - 1) / group * group) * (double)((wgs + 255) / 256) * step;
+    const long n = (wgs + 255) / 256;
+    const double share = n == 1 ? 1.0 : n * (dtype == S4 ? .75 : .925);
+    return kLaunchUs + (double)((steps + group - 1) / group * group) * share * step;
 }
 
 // The variant a call of the automatic choice runs, given the one that
-// select_variant names and its split: a small tile where the model puts it at
-// least 7% ahead, else the same. A weight matrix past the caches (64 MiB)
-// under an eight-slice tile is left there unless one row of small tiles
-// covers the small side: read once per row, it comes from memory each time
-// (FP16 64 x 8192 x 8192 45 against 40 us); and one row against one past 96
-// MiB is the memory's time either way (1 x 8192 x 8192 28.4 against 26.5).
+// select_variant names and its split: a small tile where the model puts one
+// at least 7% ahead, else the same. Small tiles that memory keeps from being
+// faster are alike: the first of them is taken (several waves on a CU stream
+// no faster than one there: FP16 16 x 8192 x 8192 29.7 us with 16 x 16 tiles,
+// 30.6 and 32.5 with K over two and four waves; INT4 32 x 4096 x 14336, far
+// from memory's time, 13.6, 9.3 and 12.0). A weight matrix past the caches
+// (64 MiB) under an eight-slice tile is left there unless one row of small
+// tiles covers the small side: read once per row, it comes from memory each
+// time (FP16 64 x 8192 x 8192 45 against 40 us); and one row against one past
+// 96 MiB is the memory's time either way (1 x 8192 x 8192 28.4 against 26.5).
 int refine(int dtype, int variant, int splits, int M, int N, int K, const void *A, const void *B, const void *C) {
     const Variant *t = table(dtype);
     const Variant &v = t[variant];
@@ -763,13 +778,18 @@ int refine(int dtype, int variant, int splits, int M, int N, int K, const void *
         have = v.kind == TILED ? tile_us(dtype, variant, splits, M, N, K) : -1;
     }
     if (have < 0) return variant;
+    const double memory = kLaunchUs + (double)bytes / kMemoryRate;
     int best = variant;
-    double best_us = 0.93 * have;
+    double first = 0.93 * have, best_us = 0;
+    bool taken = false;
     for (int cand = V_SMALL; cand < V_SMALL + kNumSmall; ++cand) {
         if (!supports(dtype, t[cand], M, N, K, A, B, C)) continue;
         if (is_deep(dtype, v) && bytes > (64L << 20) && small > t[cand].bm) continue;
         const double us = tile_us(dtype, cand, 1, M, N, K);
-        if (us < best_us) best = cand, best_us = us;
+        if (us >= first) continue;
+        const double bound = us > memory ? us : memory;
+        if (!taken || bound < best_us) best = cand, best_us = bound;
+        taken = true;
     }
     return best;
 }

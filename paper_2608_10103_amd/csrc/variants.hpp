@@ -11,6 +11,7 @@
 #include "tiled_gemm.hpp"
 #include "f6_gemm.hpp"
 #include "deep_gemm.hpp"
+#include "ksplit_gemm.hpp"
 #include "skinny_gemm.hpp"
 #include "wide_gemm.hpp"
 #include "wide_f6.hpp"
@@ -161,6 +162,13 @@ Variant skinny(const char *name) {
                    false};
 }
 
+// 16 x 16 tiles, K split over the workgroup's waves (ksplit_gemm.hpp).
+template <int DT, int KS>
+Variant ksplit(const char *name) {
+    kernel_fn f = &ksplit_gemm<DT, KS>;
+    return Variant{name, TILED, KsCfg::BM, KsCfg::BN, KsCfg::BKB, 64 * KS, reinterpret_cast<const void *>(f), false};
+}
+
 // One wave per SIMD, 256 x 256 tiles only (wide_gemm.hpp); FP16 and INT8 (no
 // kernel for INT4: fn is null and the variant supports nothing). AUX: cache
 // policy of the copy loads.
@@ -304,6 +312,8 @@ Variant generic(const char *name) {
      pipelined<DT, T32x32_w4_m16_s8, true>("spread32x32_w2x2_k128_s8_m16"),   \
      pipelined<DT, T32x32_w4_m16, true>("spread32x32_w2x2_k128_s4_m16"),      \
      pipelined<DT, T64x64_w8_m16_s5, true>("spread64x64_w2x4_k128_s5_m16"),   \
+     ksplit<DT, 2>("deep16x16_k128_s8_w2"),                                \
+     ksplit<DT, 4>("deep16x16_k128_s8_w4"),                                \
      wide_sk<DT>("wide256x256_w2x2_k128_m16_sk"),                          \
      pipelined_sk<DT, T256x256_w8_s2, false>("pipe256x256_w2x4_k128_s2_sk"), \
      pipelined_sk<DT, T128x128_w4_s4, true>("spread128x128_w2x2_k128_s4_sk"), \
@@ -312,7 +322,7 @@ Variant generic(const char *name) {
 
 // Number of entries of VARIANT_LIST, and the INT4 table's FP6 variants after
 // them (variants_s4.hip); each table checks its size against these.
-constexpr int kNumCommon = 73;
+constexpr int kNumCommon = 75;
 constexpr int kNumFp6 = 17;
 constexpr int kNumF16 = kNumCommon, kNumS8 = kNumCommon, kNumS4 = kNumCommon + kNumFp6;
 
