@@ -268,10 +268,10 @@ int mpgemm_select_splits(int dtype, int variant, int M, int N, int K);
  * one-wave-per-SIMD FP6 kernel fed by the conversion pre-pass) share the
  * last, partly filled round of a problem's tiles out over more workgroups.
  * With T tiles, G workgroups resident at once (one per CU: 256 on MI355X)
- * and T = q G + r, 0 < r <= G / 2: workgroups 0 .. q G - 1 compute one whole
- * tile each; the K-slices (KT per tile: 128 bytes of K each, or 128 k of K
- * padded to 256 for the FP6 kernel) of each of the r remaining tiles are
- * then cut into s contiguous parts, one workgroup each, s =
+ * and T = q G + r, 0 < r <= G / 2: q G tiles are computed whole, one
+ * workgroup each; the K-slices (KT per tile: 128 bytes of K each, or 128 k of
+ * K padded to 256 for the FP6 kernel) of each of the r remaining tiles are
+ * cut into s contiguous parts, one workgroup each, launched first, s =
  * round(sqrt(KT t / 5)) capped at G / r, 8 and KT / 2, where t is the time
  * of a slice in microseconds (1; 0.5 for the FP6 kernel). The last of a
  * tile's parts to finish adds the s partial tiles in part order and writes
@@ -290,7 +290,7 @@ int mpgemm_select_splits(int dtype, int variant, int M, int N, int K);
  * its schedule is on and its scratch fits, else the whole-tile kernel.
  * mpgemm_sk_schedule: the schedule a stream-K variant would use for this
  * problem on the current device (G = 256 when no device is visible):
- * *dp_tiles whole tiles first, then *parts parts per remaining tile (1:
+ * *dp_tiles whole tiles, and *parts parts per remaining tile (1:
  * stream-K off), *grid workgroups in all. hipErrorInvalidValue for an
  * invalid dtype or variant, null outputs, or a problem the variant cannot
  * run; for a variant without a stream-K schedule it reports every tile

@@ -794,6 +794,21 @@ int refine(int dtype, int variant, int splits, int M, int N, int K, const void *
     return best;
 }
 
+// FP16 with a workspace, 64 x 128 tiles chosen in two rounds where 128 x 128
+// ones are whole rounds and at most 16 more: those under their stream-K
+// schedule. 300 x 11008 x 4096 (430 tiles; 258) 50.0 against 55.3 us, x 8192
+// 90.0 against 105.8; INT8 29.7 against 28.3 (its 64 x 128 tiles are bound by
+// copies, not MFMAs), and 74 remaining tiles (FP16 700 x 7000 x 4096) 65.9
+// against 59.8.
+bool narrow_sk(int dtype, int variant, int M, int N, int K, const void *A, const void *B, const void *C) {
+    if (dtype != F16 || (variant != V_NARROW64W8 && variant != V_NARROW64W8 + 1)) return false;
+    const Variant &s = table(dtype)[V_SPREAD128W8_SK];
+    const long rest = tile_count(table(dtype)[variant], M, N) % 256;
+    const SkPlan p = sk_plan(dtype, s, M, N, K);
+    return p.on && p.dp_tiles >= 256 && tile_count(s, M, N) - p.dp_tiles <= 16 && rest > 128 &&
+           supports(dtype, s, M, N, K, A, B, C);
+}
+
 // Caller workspace. Layout: [0, 64 KiB) the split-K and stream-K tile
 // counters (zero before the first such call on a workspace; every call
 // leaves the counters it used zero again), then the zero-point row sums
@@ -1027,6 +1042,11 @@ hipError_t choose(int dtype, int variant, int splits, int M, int N, int K, const
         }
     }
     if (variant >= num_variants(dtype)) return hipErrorInvalidValue;
+    if (automatic && narrow_sk(dtype, variant, M, N, K, A, B, C)) {
+        const Variant &s = t[V_SPREAD128W8_SK];
+        if (ws_plan(s, 1, M, N, K, zero_points, sk_plan(dtype, s, M, N, K)).total <= ws_bytes)
+            variant = V_SPREAD128W8_SK;
+    }
     if (automatic) {
         // (128 x 128 tiles split over a workspace keep it: the small side
         // that they serve has no large one to spread over the CUs)

@@ -852,6 +852,20 @@ def test_stream_k_through_the_entry_point(dtype, K):
                   f"stream-K entry point {dtype} {M}x{N}x{K}")
 
 
+def test_stream_k_of_128_tiles_for_a_narrow_fp16_problem():
+    """FP16, three ragged rows of 128 x 128 tiles, 258 in all: with a workspace
+    the two past the round run split, without one the 64 x 128 tiles do."""
+    M, N, K = 260, 11000, 3072
+    assert mp.workspace_size("f16", M, N, K) > 65536 and mp.workspace_size("s8", M, N, K) == 0
+    A, B = si.gen_operands("f16", M, N, K, seed=258)
+    rows = list(range(0, M, 13))
+    ref, D = oracle_gemm("f16", A, B, rows=rows)
+    ws = mp.new_workspace(mp.workspace_size("f16", M, N, K), torch.device("cuda", 0))
+    for w in (ws, ws, None):  # the counters are left ready for the second call
+        assert_parity("f16", gpu_gemm("f16", A, B, workspace=w)[rows], ref, D, f"{M}x{N}x{K}")
+    assert int(ws[:65536].sum()) == 0
+
+
 def test_stream_k_wide_below_a_round_fp16():
     """FP16 with a workspace, 96 tiles of 256 x 256 and 128 K-slices: the
     entry point takes the one-wave-per-SIMD kernel's stream-K schedule over
