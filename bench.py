@@ -78,6 +78,7 @@ KERNEL_SOURCES = {"generic": ["generic_gemm.hpp"], "tile": ["tiled_gemm.hpp"], "
                   "deep": ["tiled_gemm.hpp", "deep_gemm.hpp"], "skinny": ["skinny_gemm.hpp"],
                   "deep16x16": ["tiled_gemm.hpp", "ksplit_gemm.hpp"],
                   "wide": ["tiled_gemm.hpp", "wide_gemm.hpp"],
+                  "wide256x128": ["tiled_gemm.hpp", "wide_gemm.hpp", "wide_narrow.hpp"],
                   "fp6wide": ["tiled_gemm.hpp", "f6_gemm.hpp", "wide_gemm.hpp", "wide_f6.hpp"],
                   "e2m3wide": ["tiled_gemm.hpp", "f6_gemm.hpp", "wide_gemm.hpp", "wide_i4.hpp"]}
 

@@ -222,9 +222,10 @@ const char *mpgemm_variant_name(int dtype, int variant);
  * Where it names a tile whose workgroups leave CUs idle or the streaming
  * kernel, the entry points (mpgemm_gemm_ws and mpgemm_gemm_noalloc too) run
  * it on one of the small tiles instead ("spread16x16...",
- * "spread32x32...", "spread64x64_w2x4...", "deep16x16...") if that is expected to be faster:
- * same product within the same bounds (integers: the same results), no
- * scratch. mpgemm_run_variant runs exactly what it names. */
+ * "spread32x32...", "spread64x64_w2x4...", "deep16x16...") if that is
+ * expected to be faster, and where more 128 x 128 tiles than CUs but no more
+ * 256 x 128 ones cover C (FP16, INT8), on those ("wide256x128..."): same
+ * product within the same bounds (integers: the same results), no scratch. mpgemm_run_variant runs exactly what it names. */
 int mpgemm_select_variant(int dtype, int M, int N, int K, const void *A, const void *B,
                           const void *C);
 

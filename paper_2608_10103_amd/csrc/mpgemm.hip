@@ -240,6 +240,7 @@ enum : int {
 // list.
 constexpr int V_WIDE_SK = kNumCommon - 5, V_PIPE256_SK = kNumCommon - 4, V_SPREAD128_SK = kNumCommon - 3,
               V_SPREAD128W8_SK = kNumCommon - 2, V_SPREAD128W8_K64_SK = kNumCommon - 1;
+constexpr int V_WIDE_NARROW = kNumCommon - 6;  // wide256x128_w2x2_k128_s3_m16
 
 // INT4-only variants follow the common list in kS4.
 constexpr int V_FP6_256_S2 = kNumCommon + 1;  // fp6pipe256x256_w2x4_k128_s2
@@ -794,19 +795,51 @@ int refine(int dtype, int variant, int splits, int M, int N, int K, const void *
     return best;
 }
 
-// FP16 with a workspace, 64 x 128 tiles chosen in two rounds where 128 x 128
-// ones are whole rounds and at most 16 more: those under their stream-K
-// schedule. 300 x 11008 x 4096 (430 tiles; 258) 50.0 against 55.3 us, x 8192
-// 90.0 against 105.8; INT8 29.7 against 28.3 (its 64 x 128 tiles are bound by
-// copies, not MFMAs), and 74 remaining tiles (FP16 700 x 7000 x 4096) 65.9
-// against 59.8.
+constexpr long kSkRowBytes = 8192;
+
+// FP16 with a workspace and rows longer than 8 KiB (narrow_wide serves the
+// shorter), 64 x 128 tiles chosen in two rounds where 128 x 128 ones are whole
+// rounds and at most 16 more: those under their stream-K schedule. 300 x 11008
+// x 8192 (430 tiles; 258) 88.6 against 105.4 us and 103.6 with 256 x 128 tiles;
+// INT8 29.7 against 28.3 (its 64 x 128 tiles are bound by copies, not MFMAs),
+// and 74 remaining tiles (FP16 700 x 7000 x 4096) 65.9 against 59.8.
 bool narrow_sk(int dtype, int variant, int M, int N, int K, const void *A, const void *B, const void *C) {
     if (dtype != F16 || (variant != V_NARROW64W8 && variant != V_NARROW64W8 + 1)) return false;
+    if (row_bytes(dtype, K) <= kSkRowBytes) return false;
     const Variant &s = table(dtype)[V_SPREAD128W8_SK];
     const long rest = tile_count(table(dtype)[variant], M, N) % 256;
     const SkPlan p = sk_plan(dtype, s, M, N, K);
     return p.on && p.dp_tiles >= 256 && tile_count(s, M, N) - p.dp_tiles <= 16 && rest > 128 &&
            supports(dtype, s, M, N, K, A, B, C);
+}
+
+// FP16 and INT8 with more 128 x 128 tiles than CUs but no more 256 x 128 ones:
+// one round of those (wide_narrow.hpp), whichever tile was chosen before. Two
+// rounds of 128 x 128 take 1.2 to 1.45 times as long, whole or split (us, 128
+// x 128 against 256 x 128): FP16 2048 x 4096 x 4096 78.8 / 59.4, x 1024 29.5 /
+// 20.8, 1100 x 4096 x 4096 60.5 / 47.3, with a workspace 54.9 / 47.3; INT8 45.6
+// / 32.9, 17.4 / 14.3, 34.0 / 28.5, 34.0 / 28.5. 256 x 256 tiles split over a
+// workspace: FP16 2048 x 4096 x 14336 224.5 / 199.9. With at most 256 tiles of
+// 128 x 128 one round of them is ahead (FP16 1024 x 4096 x 4096 40.6 / 44.0,
+// INT8 23.7 / 25.5), and so it is below eight slices, where the longer start
+// and end of the large tile show (INT8 2050 x 2050 x 256 10.6 / 11.3). 64 x 128
+// tiles, taken where 128 x 128 ones would be padding by a quarter: FP16 300 x
+// 11008 x 4096 57.3 / 48.6, INT8 29.0 / 27.0. A stream-K schedule of 128 x 128
+// tiles with at most 16 of them past the round stays where rows are longer than
+// 8 KiB: FP16 380 x 11008 x 8192 90.9 / 104.1, 300 x 11008 x 4608 56.2 / 61.4,
+// but x 4096 51.2 / 49.1 and 1280 x 4096 x 8192 (320 tiles) 114.2 / 101.6.
+bool narrow_wide(int dtype, int variant, int M, int N, int K, const void *A, const void *B, const void *C) {
+    if (dtype == S4) return false;
+    const int base = sk_base(variant) >= 0 ? sk_base(variant) : variant;
+    if (base != V_SPREAD128W8 && base != V_SPREAD128W8_K64 && base != V_WIDE && base != V_PIPE256_W2X4 &&
+        base != V_NARROW64W8 && base != V_NARROW64W8 + 1)
+        return false;
+    const Variant *t = table(dtype), &w = t[V_WIDE_NARROW];
+    if ((variant == V_SPREAD128W8_SK || variant == V_SPREAD128W8_K64_SK) && row_bytes(dtype, K) > kSkRowBytes &&
+        tile_count(t[variant], M, N) <= 256 + 16)
+        return false;
+    return tile_count(w, M, N) <= 256 && tile_count(t[V_SPREAD128W8], M, N) > 256 &&
+           row_bytes(dtype, K) >= 8L * w.bkb && supports(dtype, w, M, N, K, A, B, C);
 }
 
 // Caller workspace. Layout: [0, 64 KiB) the split-K and stream-K tile
@@ -1042,11 +1075,12 @@ hipError_t choose(int dtype, int variant, int splits, int M, int N, int K, const
         }
     }
     if (variant >= num_variants(dtype)) return hipErrorInvalidValue;
-    if (automatic && narrow_sk(dtype, variant, M, N, K, A, B, C)) {
-        const Variant &s = t[V_SPREAD128W8_SK];
-        if (ws_plan(s, 1, M, N, K, zero_points, sk_plan(dtype, s, M, N, K)).total <= ws_bytes)
-            variant = V_SPREAD128W8_SK;
-    }
+    const Variant &nsk = t[V_SPREAD128W8_SK];
+    if (automatic && narrow_sk(dtype, variant, M, N, K, A, B, C) &&
+        ws_plan(nsk, 1, M, N, K, zero_points, sk_plan(dtype, nsk, M, N, K)).total <= ws_bytes)
+        variant = V_SPREAD128W8_SK;
+    else if (automatic && narrow_wide(dtype, variant, M, N, K, A, B, C))
+        variant = V_WIDE_NARROW;
     if (automatic) {
         // (128 x 128 tiles split over a workspace keep it: the small side
         // that they serve has no large one to spread over the CUs)

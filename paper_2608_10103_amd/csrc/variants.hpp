@@ -14,6 +14,7 @@
 #include "ksplit_gemm.hpp"
 #include "skinny_gemm.hpp"
 #include "wide_gemm.hpp"
+#include "wide_narrow.hpp"
 #include "wide_f6.hpp"
 #include "wide_i4.hpp"
 #include "stream_k.hpp"
@@ -183,6 +184,18 @@ Variant wide(const char *name) {
     return Variant{name, WIDE, WideCfg::BM, WideCfg::BN, WideCfg::BKB, WideCfg::NTHREADS, f, false, fe};
 }
 
+// Its 256 x 128 tile (wide_narrow.hpp), FP16 and INT8.
+template <int DT>
+Variant wide_narrow(const char *name) {
+    const void *f = nullptr, *fe = nullptr;
+    if constexpr (DT == F16 || DT == S8) {
+        kernel_fn k = &wide_narrow_gemm<DT, true>, ke = &wide_narrow_gemm<DT, false>;
+        f = reinterpret_cast<const void *>(k);
+        fe = reinterpret_cast<const void *>(ke);
+    }
+    return Variant{name, WIDE, WideNarrowCfg::BM, WideNarrowCfg::BN, WideNarrowCfg::BKB, WideNarrowCfg::NTHREADS, f, false, fe};
+}
+
 // Stream-K schedule of the one-wave-per-SIMD kernel (stream_k.hpp); FP16
 // and INT8 only, like wide().
 template <int DT>
@@ -314,6 +327,7 @@ Variant generic(const char *name) {
      pipelined<DT, T64x64_w8_m16_s5, true>("spread64x64_w2x4_k128_s5_m16"),   \
      ksplit<DT, 2>("deep16x16_k128_s8_w2"),                                \
      ksplit<DT, 4>("deep16x16_k128_s8_w4"),                                \
+     wide_narrow<DT>("wide256x128_w2x2_k128_s3_m16"),                      \
      wide_sk<DT>("wide256x256_w2x2_k128_m16_sk"),                          \
      pipelined_sk<DT, T256x256_w8_s2, false>("pipe256x256_w2x4_k128_s2_sk"), \
      pipelined_sk<DT, T128x128_w4_s4, true>("spread128x128_w2x2_k128_s4_sk"), \
@@ -322,7 +336,7 @@ Variant generic(const char *name) {
 
 // Number of entries of VARIANT_LIST, and the INT4 table's FP6 variants after
 // them (variants_s4.hip); each table checks its size against these.
-constexpr int kNumCommon = 75;
+constexpr int kNumCommon = 76;
 constexpr int kNumFp6 = 17;
 constexpr int kNumF16 = kNumCommon, kNumS8 = kNumCommon, kNumS4 = kNumCommon + kNumFp6;
 

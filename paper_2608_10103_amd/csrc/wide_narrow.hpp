@@ -1,0 +1,318 @@
+// wide_narrow.hpp - one wave per SIMD, 256 x 128 tile (FP16 and INT8).
+//
+// The half tile of wide_gemm.hpp, for problems with too few 256 x 256 tiles
+// to give every CU one. 2 x 2 waves of 128 x 64 on 16x16 MFMAs (32
+// accumulator blocks), K in 128-byte slices, the copy loads and the padded
+// 8-row blocks of wide_gemm.hpp.
+//
+// What bounds it is the LDS: a slice costs 48 KB of copies and 96 KB of
+// operand reads for 256 x 128 of C. Two workgroups of 128 x 128 tiles with
+// eight waves of 64 x 32, the kernel otherwise taken here, move 64 KB and
+// 192 KB for the same part of C. FP16 2048 x 4096 x 4096 78.8 -> 59.4 us, INT8
+// 45.6 -> 32.9 (2.1 POP/s); 1280 x 5120 x 5120 83.8 -> 64.2 and 46.3 -> 34.0.
+//
+// The tile leaves room for three slices, so one barrier per slice is enough:
+//   chunk 0: reads of chunk 1 of slice kt; copy loads 6-11 of slice kt + 2;
+//   barrier: every wave has read slice kt, and slice kt + 1 has landed (the
+//     12 loads of slice kt + 2 are in flight);
+//   chunk 1: reads of chunk 0 of slice kt + 1; copy loads 0-5 of slice kt + 3
+//     into the buffer of slice kt.
+// Past the end of K the loads fetch the last slice again into a buffer
+// nobody reads. M and N may be ragged, as in wide_gemm.hpp; K bytes must be
+// a multiple of 128.
+#pragma once
+
+#include "wide_gemm.hpp"
+
+namespace mpg {
+
+struct WideNarrowCfg {
+    static constexpr int BM = 256, BN = 128, BKB = 128, MS = 16, NTHREADS = 256;
+    static constexpr int FM = 8, FN = 4;
+    static constexpr int BLK = WideCfg::BLK;
+    static constexpr int STAGE = 48 * BLK;  // 384 rows: A 256, B 128
+    static constexpr int TERMS = 3 * STAGE;  // scales and zero points (EpiLds)
+    static constexpr int LDS_BYTES = TERMS + EpiLds<BM, BN>::FLAG + 4 * NTHREADS / 64;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS capacity");
+};
+
+// The copies of one wave: 8 blocks of an A panel (128 rows), 4 of the B panel
+struct WideNarrowCopy {
+    const uint8_t *a, *b;     // the panels
+    int a_bytes, b_bytes;     // their rows inside the matrix
+    uint32_t voff;            // lane: row 16 (l / 8) of the load, bytes 16 (l % 8) ..
+    int kb;                   // row pitch (bytes)
+    int ja, jb;               // the wave's first block in either panel
+    uint8_t *da, *db;         // and where it lies in buffer 0
+};
+
+// copy load j (0..11: A 0..7, B 8..11) of slice ks into the buffer at `buf`
+template <int J>
+__device__ __forceinline__ void wn_load(const WideNarrowCopy &c, int ks, int buf) {
+    typedef WideNarrowCfg T;
+    if constexpr (J < 8)
+        wide_copy(c.a, c.a_bytes, c.da + buf + J * T::BLK, c.voff, ks * T::BKB + (c.ja + J) * c.kb);
+    else
+        wide_copy(c.b, c.b_bytes, c.db + buf + (J - 8) * T::BLK, c.voff, ks * T::BKB + (c.jb + J - 8) * c.kb);
+}
+
+// One K-chunk: eight groups of four MFMAs on (a, b); three reads of the next
+// operands in each of groups 0-3; copy loads J0 .. J0 + 5 of slice ks, three
+// in every four groups.
+template <int DT, int J0>
+__device__ __forceinline__ void wn_chunk(const i32x4 (&a)[8], const i32x4 (&b)[4],
+                                         typename Acc<DT, 16>::type (&acc)[8][4], i32x4 (&na)[8], i32x4 (&nb)[4],
+                                         const uint8_t *rab, const uint8_t *rbb, const WideNarrowCopy &c, int ks,
+                                         int buf) {
+    static_for<8>([&](auto gg) __attribute__((always_inline)) {
+        constexpr int g = decltype(gg)::value;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) wide_mfma<DT>(a[g], b[j], acc[g][j]);
+        if constexpr (g < 4) {
+            static_for<3>([&](auto xx) __attribute__((always_inline)) {
+                constexpr int q = 3 * g + decltype(xx)::value;  // run: B 0..3, then A 0..7
+                if constexpr (q < 4) nb[q] = *reinterpret_cast<const i32x4 *>(rbb + q * WideNarrowCfg::BKB);
+                else na[q - 4] = *reinterpret_cast<const i32x4 *>(rab + (q - 4) * WideNarrowCfg::BKB);
+            });
+        }
+        if constexpr (g % 4 != 3) wn_load<J0 + g - g / 4>(c, ks, buf);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+// Accumulators of a finished tile to C. PLAIN: raw sums of a whole tile,
+// stored straight from the accumulators; otherwise scales, zero points,
+// output types and ragged edges (see EpiParams, and epi_store_tile for the
+// arithmetic). These go through LDS, from which a loop stores two whole rows
+// at a time: with one wave per SIMD nothing hides the first fetch of
+// epi_store_tile's straight-line code for 128 values a lane, with which
+// an FP16 300 x 384 x 512 call took 18.3 us against 11.9 and 300 x 11008 x 4096
+// 77.5 against 49.6.
+template <int DT, bool PLAIN>
+__device__ __forceinline__ void wn_store(const EpiParams &e, void *C, const typename Acc<DT, 16>::type (&acc)[8][4],
+                                         uint8_t *lds, bool wide, int tm, int tn, int M, int N) {
+    typedef WideNarrowCfg T;
+    typedef typename Acc<DT, 16>::out out_t;
+    typedef out_t out4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane % 16, h = lane / 16;
+    // element (i, j, v) of this lane: row 16 i + 4 h + v, column 16 j of the
+    // wave's part, which starts at (lr, lc)
+    const int lr = (wave / 2) * 128 + 4 * h, lc = (wave % 2) * 64 + r;
+    const long row_t = (long)tm * T::BM, col_t = (long)tn * T::BN;
+    if constexpr (PLAIN) {
+        out_t *base = reinterpret_cast<out_t *>(C) + (row_t + lr) * N + col_t + lc;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                out_t *rowp = base + (long)(16 * i + v) * N;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rowp[16 * j] = acc[i][j][v];
+            }
+        return;
+    }
+    // sums in the place of the slices, rows padded by 16 bytes: the four lane
+    // groups write to distinct banks
+    typedef EpiLds<T::BM, T::BN> L;
+    constexpr int PITCH = 4 * T::BN + 16;
+    static_assert(T::BM * PITCH <= T::TERMS, "LDS");
+    const uint8_t *te = lds + T::TERMS;
+    __syncthreads();  // every wave has read its operands, every copy has landed
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<out_t *>(lds + (lr + 16 * i + v) * PITCH + 4 * (lc + 16 * j)) = acc[i][j][v];
+    const bool zp = DT != F16 && (e.zero_a || e.zero_b);
+    const bool terms = zp || e.scale_a || e.scale_b;
+    __syncthreads();
+
+    // lane: columns 4 (l % 32) .. + 3 of row l / 32 of the wave's two
+    const int c0 = 4 * (lane % 32);
+    const long col = col_t + c0;
+    const int cols = (int)min((long)N - col, 4L);
+    f32x4 sb = {1.0f, 1.0f, 1.0f, 1.0f};
+    i32x4 zb = {0, 0, 0, 0};
+    long long cs[4] = {0, 0, 0, 0};
+    if (terms) sb = *reinterpret_cast<const f32x4 *>(te + L::SB + 4 * c0);
+    if (zp) {
+        zb = *reinterpret_cast<const i32x4 *>(te + L::ZB + 4 * c0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cs[j] = *reinterpret_cast<const long long *>(te + L::CS + 8 * (c0 + j));
+    }
+    if (cols <= 0) return;
+    const int rows = (int)min((long)M - row_t, (long)T::BM);
+    const auto put = [&](auto *p, auto y) __attribute__((always_inline)) {
+        typedef decltype(y) vec;
+        typedef vec vec_any __attribute__((aligned(sizeof(*p))));
+        if (cols == 4) {
+            *reinterpret_cast<vec_any *>(p) = y;
+        } else {
+            p[0] = y[0];
+            if (cols > 1) p[1] = y[1];
+            if (cols > 2) p[2] = y[2];
+        }
+    };
+    // four rows of a lane at a time: their reads are under way together (rows
+    // past M are read, not stored; without terms the reads of them mean nothing)
+    for (int r0 = 2 * wave + lane / 32; r0 < rows; r0 += 32) {
+        out4 c[4];
+        float sa[4];
+        int za[4] = {}, ra[4] = {};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            c[u] = *reinterpret_cast<const out4 *>(lds + (r0 + 8 * u) * PITCH + 4 * c0);
+            sa[u] = *reinterpret_cast<const float *>(te + L::SA + 4 * (r0 + 8 * u));
+            if constexpr (DT != F16) {
+                za[u] = *reinterpret_cast<const int *>(te + L::ZA + 4 * (r0 + 8 * u));
+                ra[u] = *reinterpret_cast<const int *>(te + L::RA + 4 * (r0 + 8 * u));
+            }
+        }
+        const auto store = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r0 + 8 * u < rows) f(u, (row_t + r0 + 8 * u) * N + col);
+        };
+        if (e.out == OUT_PLAIN) {
+            store([&](int u, long at) __attribute__((always_inline)) { put(reinterpret_cast<out_t *>(C) + at, c[u]); });
+            continue;
+        }
+        f32x4 x[4];
+        if (!zp) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[u][j] = (float)c[u][j];
+        } else if (!wide) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[u][j] = (float)fma(-(double)za[u], (double)(int)cs[j],
+                                         fma(-(double)zb[j], (double)ra[u], (double)c[u][j]));
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[u][j] = (float)((long long)c[u][j] - (long long)zb[j] * ra[u] - za[u] * cs[j]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[u][j] = x[u][j] * (terms ? sa[u] : 1.0f) * sb[j];
+        if (e.out == OUT_F32) {
+            store([&](int u, long at) __attribute__((always_inline)) { put(reinterpret_cast<float *>(C) + at, x[u]); });
+        } else if (e.out == OUT_F16) {
+            typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+            store([&](int u, long at) __attribute__((always_inline)) {
+                put(reinterpret_cast<_Float16 *>(C) + at,
+                    h4{(_Float16)x[u][0], (_Float16)x[u][1], (_Float16)x[u][2], (_Float16)x[u][3]});
+            });
+        } else {
+            typedef uint16_t u4 __attribute__((ext_vector_type(4)));
+            store([&](int u, long at) __attribute__((always_inline)) {
+                put(reinterpret_cast<uint16_t *>(C) + at, u4{f32_to_bf16_rne(x[u][0]), f32_to_bf16_rne(x[u][1]),
+                                                             f32_to_bf16_rne(x[u][2]), f32_to_bf16_rne(x[u][3])});
+            });
+        }
+    }
+}
+
+// PLAIN: raw sums of whole tiles to the row-major output; otherwise the
+// shared epilogue (see EpiParams).
+template <int DT, bool PLAIN>
+__global__ __launch_bounds__(WideNarrowCfg::NTHREADS, 1) void wide_narrow_gemm(
+    const uint8_t *__restrict__ A, const uint8_t *__restrict__ B, void *__restrict__ Cv, int M, int N, int Kb,
+    int tiles_m, int tiles_n, EpiParams epi) {
+    static_assert(DT == F16 || DT == S8, "FP16 and INT8");
+    typedef WideNarrowCfg T;
+    typedef typename Acc<DT, 16>::type acc_t;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[PLAIN ? T::TERMS : T::LDS_BYTES];
+    int tm, tn;
+    tile_coords(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, 4, tm, tn);
+    // opaque thread id: see pf_accumulate
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane % 16, h = lane / 16;
+    const int wm = wave / 2, wn = wave % 2;
+    const int KT = Kb / T::BKB;
+
+    // wave w copies blocks 8 (w % 2) .. + 7 of A panel w / 2 and blocks 4 w ..
+    // + 3 of the B panel. The buffer bounds cover the panels' rows inside the
+    // matrix (scalar registers: see wide_accumulate).
+    WideNarrowCopy c;
+    const int arow = tm * T::BM + wm * 128, brow = tn * T::BN;
+    c.a = A + (size_t)arow * Kb;
+    c.b = B + (size_t)brow * Kb;
+    c.a_bytes = __builtin_amdgcn_readfirstlane(min(max(M - arow, 0), 128) * Kb);
+    c.b_bytes = __builtin_amdgcn_readfirstlane(min(N - brow, 128) * Kb);
+    c.voff = (uint32_t)((lane / 8) * 16 * Kb + (lane % 8) * 16);
+    c.kb = Kb;
+    c.ja = 8 * wn;
+    c.jb = 4 * wave;
+    c.da = lds + (wm * 16 + c.ja) * T::BLK;
+    c.db = lds + (32 + c.jb) * T::BLK;
+    // run p of A (rows 128 wm + 16 p + r): position p of block 16 wm + r; of B
+    // (rows 64 wn + 16 p + r): position 4 wn + p of block r
+    const uint8_t *ra0 = lds + (wm * 16 + r) * T::BLK + h * 16;
+    const uint8_t *rb0 = lds + (32 + r) * T::BLK + 4 * wn * T::BKB + h * 16;
+
+    // accumulators: see wide_accumulate
+    acc_t acc[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = acc_t{};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
+    asm volatile("s_nop 4" ::: "memory");
+
+    // prologue: slices 0 and 1, loads 0-5 of slice 2; wait for slice 0
+    static_for<12>([&](auto j) __attribute__((always_inline)) { wn_load<decltype(j)::value>(c, 0, 0); });
+    static_for<12>([&](auto j) __attribute__((always_inline)) {
+        wn_load<decltype(j)::value>(c, min(1, KT - 1), T::STAGE);
+    });
+    static_for<6>([&](auto j) __attribute__((always_inline)) {
+        wn_load<decltype(j)::value>(c, min(2, KT - 1), 2 * T::STAGE);
+    });
+    // the scales and zero points of the output stage, while the slices come
+    bool wide = false;
+    if constexpr (!PLAIN)
+        if (epi.scale_a || epi.scale_b || epi.zero_a || epi.zero_b)
+            wide = epi_terms<DT, T::BM, T::BN, T::NTHREADS>(epi, lds + T::TERMS, (long)tm * T::BM, (long)tn * T::BN, M, N);
+    asm volatile("s_waitcnt vmcnt(18)\n\ts_barrier" ::: "memory");
+    i32x4 ra[2][8], rb[2][4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) rb[0][p] = *reinterpret_cast<const i32x4 *>(rb0 + p * T::BKB);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) ra[0][p] = *reinterpret_cast<const i32x4 *>(ra0 + p * T::BKB);
+
+    int cur = 0, nxt = T::STAGE, thr = 2 * T::STAGE;  // buffers of slices kt, kt + 1, kt + 2
+    for (int kt = 0; kt < KT; ++kt) {
+        wn_chunk<DT, 6>(ra[0], rb[0], acc, ra[1], rb[1], ra0 + cur + 64, rb0 + cur + 64, c, min(kt + 2, KT - 1), thr);
+        asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        wn_chunk<DT, 0>(ra[1], rb[1], acc, ra[0], rb[0], ra0 + nxt, rb0 + nxt, c, min(kt + 3, KT - 1), cur);
+        const int old = cur;
+        cur = nxt;
+        nxt = thr;
+        thr = old;
+    }
+    // the last copies and MFMA results: see wide_accumulate
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
+
+    wn_store<DT, PLAIN>(epi, Cv, acc, lds, wide, tm, tn, M, N);
+}
+
+}  // namespace mpg

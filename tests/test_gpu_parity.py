@@ -854,8 +854,9 @@ def test_stream_k_through_the_entry_point(dtype, K):
 
 def test_stream_k_of_128_tiles_for_a_narrow_fp16_problem():
     """FP16, three ragged rows of 128 x 128 tiles, 258 in all: with a workspace
-    the two past the round run split, without one the 64 x 128 tiles do."""
-    M, N, K = 260, 11000, 3072
+    and K past 4096 the two past the round run split, without one 256 x 128
+    tiles run."""
+    M, N, K = 260, 11000, 4608
     assert mp.workspace_size("f16", M, N, K) > 65536 and mp.workspace_size("s8", M, N, K) == 0
     A, B = si.gen_operands("f16", M, N, K, seed=258)
     rows = list(range(0, M, 13))
@@ -948,6 +949,30 @@ def test_zero_points_of_any_size_and_row_length(dtype, K, sides):
     C = _run_scaled(dtype, A, B, "f32", sa, sb, za, zb)
     _, exact, D = oracle.gemm_scaled(dtype, A, B, "f32", sa, sb, za, zb)
     assert_scaled(C, exact, D, "f32", f"{dtype} {M}x{N}x{K} zero points {sides}")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "s8"])
+@pytest.mark.parametrize("M,N", [(1100, 4093), (2048, 4096), (300, 11008), (1300, 4094), (4095, 1281)])
+@pytest.mark.parametrize("out", OUTS)
+def test_one_round_of_256x128_tiles_through_the_entry_points(dtype, M, N, out):
+    """More 128 x 128 tiles than CUs and no more 256 x 128 ones: raw sums,
+    scales and zero points, some past 2^21, in whole and ragged tiles."""
+    K = 1024
+    A, B = si.gen_operands(dtype, M, N, K, seed=N)
+    rows = list(range(0, M, 61)) + [M - 1]
+    ref, D = oracle_gemm(dtype, A, B, rows=rows)
+    assert_parity(dtype, gpu_gemm(dtype, A, B)[rows], ref, D, f"{dtype} {M}x{N}x{K}")
+    for big in (False, True):
+        if big and (dtype == "f16" or out != "f32"):
+            continue
+        sa, sb, za, zb = _scales(dtype, M, N, K, dtype != "f16")
+        if big:
+            za[[0, M // 2, M - 1]] = (1 << 21) - 1, -(1 << 21), 1 << 26
+            zb[[1, N - 1]] = -(1 << 25), 1 << 21
+        C = _run_scaled(dtype, A, B, out, sa, sb, za, zb)
+        za_r = za[rows] if za is not None else None
+        _, exact, D = oracle.gemm_scaled(dtype, A[rows], B, out, sa[rows], sb, za_r, zb)
+        assert_scaled(C[rows], exact, D, out, f"{dtype} {M}x{N}x{K} {out} {big}")
 
 
 @pytest.mark.parametrize("dtype", DTYPES)
