@@ -431,7 +431,7 @@ typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 // bytes) for the zero-point terms: RA rows of A, then RB rows of B (either may
 // be none), a wave per row, 1 KiB of it per load and dot products with ones.
 // Bound by reading the operands once: 16 MiB of B (4096 rows of 4096) 12.7 ->
-// 6.3 us against one block per row that read a byte per lane.
+// 4.8-6.3 us against one block per row that read a byte per lane.
 constexpr int ROW_SUMS_WAVES = 4;
 template <int DT>
 __global__ __launch_bounds__(64 * ROW_SUMS_WAVES) void row_sums(const uint8_t *__restrict__ A, long RA,
