@@ -688,8 +688,9 @@ int select_variant(int dtype, int M, int N, int K, const void *A, const void *B,
 // .. 14336 x 1536 .. 14336, 256^3 .. 1408^3): the pick is within 3% of the
 // fastest tile on average and 1.28 (FP16), 1.27 (INT8), 1.21 (INT4) times as
 // fast as the tile chosen before without a workspace, 1.15, 1.22 and 1.18
-// with one (K split). INT4's slices hold twice the k: two MFMAs and a decode
-// per run.
+// with one (K split); FP16's figures are those before the calls of the
+// streaming kernel stayed there (refine). INT4's slices hold twice the k: two
+// MFMAs and a decode per run.
 struct SliceCost {
     int variant, resident;
     double alone, shared, alone4, shared4;  // FP16 and INT8; INT4
@@ -766,6 +767,11 @@ double skinny_us(int dtype, int variant, int M, int N, int K) {
 // tiles covers the small side: read once per row, it comes from memory each
 // time (FP16 64 x 8192 x 8192 45 against 40 us); and one row against one past
 // 96 MiB is the memory's time either way (1 x 8192 x 8192 28.4 against 26.5).
+// FP16 never takes a tile that adds up K in fewer partial sums than the
+// kernel it replaces: each partial sum rounds over its whole length, and the
+// streaming kernel's eight are the more exact (error in the 2-norm, 3 x 2496 x
+// 6400: eight 1.9e-7, four 2.6e-7, two 3.7e-7, one 5.1e-7; that kernel 10.4
+// us, four 7.1). Integer sums are exact either way.
 int refine(int dtype, int variant, int splits, int M, int N, int K, const void *A, const void *B, const void *C) {
     const Variant *t = table(dtype);
     const Variant &v = t[variant];
@@ -773,6 +779,7 @@ int refine(int dtype, int variant, int splits, int M, int N, int K, const void *
     const long bytes = (long)large * row_bytes(dtype, K);
     double have;
     if (v.kind == SKINNY) {
+        if (dtype == F16) return variant;
         if (small == 1 && bytes > (96L << 20) && large <= 16 * 512) return variant;
         have = skinny_us(dtype, variant, M, N, K);
     } else {
@@ -785,6 +792,8 @@ int refine(int dtype, int variant, int splits, int M, int N, int K, const void *
     bool taken = false;
     for (int cand = V_SMALL; cand < V_SMALL + kNumSmall; ++cand) {
         if (!supports(dtype, t[cand], M, N, K, A, B, C)) continue;
+        const int sums = cand == V_KSPLIT ? 2 : cand == V_KSPLIT + 1 ? 4 : 1;
+        if (dtype == F16 && sums < splits) continue;
         if (is_deep(dtype, v) && bytes > (64L << 20) && small > t[cand].bm) continue;
         const double us = tile_us(dtype, cand, 1, M, N, K);
         if (us >= first) continue;
@@ -818,8 +827,9 @@ bool narrow_sk(int dtype, int variant, int M, int N, int K, const void *A, const
 // rounds of 128 x 128 take 1.2 to 1.45 times as long, whole or split (us, 128
 // x 128 against 256 x 128): FP16 2048 x 4096 x 4096 78.8 / 59.4, x 1024 29.5 /
 // 20.8, 1100 x 4096 x 4096 60.5 / 47.3, with a workspace 54.9 / 47.3; INT8 45.6
-// / 32.9, 17.4 / 14.3, 34.0 / 28.5, 34.0 / 28.5. 256 x 256 tiles split over a
-// workspace: FP16 2048 x 4096 x 14336 224.5 / 199.9. With at most 256 tiles of
+// / 32.9, 17.4 / 14.3, 34.0 / 28.5, 34.0 / 28.5. FP16 whose tiles are mostly
+// split over a workspace keeps them (2048 x 4096 x 14336, 256 x 256 tiles, 224.5
+// / 199.9): two partial sums round less than one. With at most 256 tiles of
 // 128 x 128 one round of them is ahead (FP16 1024 x 4096 x 4096 40.6 / 44.0,
 // INT8 23.7 / 25.5), and so it is below eight slices, where the longer start
 // and end of the large tile show (INT8 2050 x 2050 x 256 10.6 / 11.3). 64 x 128
@@ -838,6 +848,11 @@ bool narrow_wide(int dtype, int variant, int M, int N, int K, const void *A, con
     if ((variant == V_SPREAD128W8_SK || variant == V_SPREAD128W8_K64_SK) && row_bytes(dtype, K) > kSkRowBytes &&
         tile_count(t[variant], M, N) <= 256 + 16)
         return false;
+    if (dtype == F16 && sk_base(variant) >= 0) {
+        const SkPlan p = sk_plan(dtype, t[variant], M, N, K);
+        const long tiles = tile_count(t[variant], M, N);
+        if (p.on && 2 * (tiles - p.dp_tiles) > tiles) return false;
+    }
     return tile_count(w, M, N) <= 256 && tile_count(t[V_SPREAD128W8], M, N) > 256 &&
            row_bytes(dtype, K) >= 8L * w.bkb && supports(dtype, w, M, N, K, A, B, C);
 }

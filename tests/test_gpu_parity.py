@@ -852,6 +852,16 @@ def test_stream_k_through_the_entry_point(dtype, K):
                   f"stream-K entry point {dtype} {M}x{N}x{K}")
 
 
+@pytest.mark.parametrize("M,N,K", [(3, 2496, 6400), (1, 4096, 4096), (16, 2048, 4096)])
+def test_fp16_streaming_calls_keep_their_partial_sums(M, N, K):
+    """FP16 sums of a few rows stay those of the streaming kernel, whose eight
+    partial sums along K round less than a longer walk's."""
+    A, B = si.gen_operands("f16", M, N, K, seed=M)
+    streamed = gpu_gemm("f16", A, B, variant=mp.select_variant("f16", M, N, K))
+    assert np.array_equal(gpu_gemm("f16", A, B), streamed)
+    assert np.array_equal(gpu_gemm("f16", A, B, workspace="auto"), streamed)
+
+
 def test_stream_k_of_128_tiles_for_a_narrow_fp16_problem():
     """FP16, three ragged rows of 128 x 128 tiles, 258 in all: with a workspace
     and K past 4096 the two past the round run split, without one 256 x 128
